@@ -1,0 +1,135 @@
+// Workspaces of the digit sorts (host code, no HIP: the allocator is a
+// parameter, so the policy is tested on the CPU).
+//
+// A sort on stream S takes S's buffer.  Work on one stream is ordered, so the
+// next sort on S may write the buffer as soon as it runs; a buffer that is
+// replaced is freed in stream order, behind the work that uses it.  A buffer
+// is lent to one call at a time: another thread that enqueues on the same
+// stream meanwhile gets a buffer of its own, since its launches may fall
+// between this call's.
+//
+// What is kept is bounded: at most kKeepBytes a stream, kKeepTotal and
+// kKeepSlots in all.  Anything beyond is allocated for the one call and freed
+// in stream order behind it, and a stream whose calls have long needed an
+// eighth of its buffer or less gives it back for a smaller one.
+#pragma once
+
+#include <stddef.h>
+
+#include <mutex>
+#include <vector>
+
+namespace bitonic {
+
+// Alloc: `void* alloc(int dev, void* stream, size_t bytes)` (nullptr on
+// failure) and `bool free(int dev, void* stream, void* ptr)`, stream-ordered.
+template <class Alloc>
+class WorkspaceCache {
+ public:
+  static constexpr size_t kMinBytes = size_t(1) << 20;
+  static constexpr size_t kKeepBytes = size_t(256) << 20;
+  static constexpr size_t kKeepTotal = size_t(2) << 30;
+  static constexpr size_t kKeepSlots = 32;
+  static constexpr int kShrinkCalls = 64;
+
+  explicit WorkspaceCache(Alloc a = Alloc{}) : alloc_(a) {}
+
+  // A buffer of at least `bytes` for work on (dev, stream), nullptr if there
+  // is none to be had.  keep == false: never a kept one (a stream handle that
+  // names another stream in every thread).  Every buffer is given back with
+  // release() once the call's work is enqueued.
+  void* acquire(int dev, void* stream, size_t bytes, bool keep = true) {
+    std::lock_guard<std::mutex> lock(mu_);
+    for (size_t i = 0; i < parked_.size(); ++i) {
+      // a buffer whose free failed: its stream's work is still ordered
+      Slot& s = parked_[i];
+      if (s.dev != dev || s.stream != stream || s.lent || !keep) continue;
+      if (s.bytes >= bytes) {
+        s.lent = true;
+        return s.ptr;
+      }
+      if (alloc_.free(dev, stream, s.ptr)) parked_.erase(parked_.begin() + (ptrdiff_t)i--);
+    }
+    if (keep && bytes <= kKeepBytes) {
+      Slot* s = find(dev, stream);
+      if (s && !s->lent) {
+        s->small = bytes <= s->bytes / 8 ? s->small + 1 : 0;
+        if (s->bytes >= bytes && s->small < kShrinkCalls) {
+          s->lent = true;
+          return s->ptr;
+        }
+        const size_t want = rounded(bytes);
+        if (kept_ - s->bytes + want <= kKeepTotal) {
+          if (void* p = alloc_.alloc(dev, stream, want)) {
+            give_back(*s);
+            kept_ += want - s->bytes;
+            *s = Slot{dev, stream, p, want, 0, true};
+            return p;
+          }
+          if (s->bytes >= bytes) {
+            s->lent = true;
+            return s->ptr;
+          }
+          return nullptr;
+        }
+      } else if (!s && slots_.size() < kKeepSlots && kept_ + rounded(bytes) <= kKeepTotal) {
+        const size_t want = rounded(bytes);
+        void* p = alloc_.alloc(dev, stream, want);
+        if (!p) return nullptr;
+        slots_.push_back(Slot{dev, stream, p, want, 0, true});
+        kept_ += want;
+        return p;
+      }
+    }
+    return alloc_.alloc(dev, stream, bytes);
+  }
+
+  // After the work that uses p is enqueued on (dev, stream).
+  void release(int dev, void* stream, void* p, size_t bytes) {
+    std::lock_guard<std::mutex> lock(mu_);
+    for (auto* list : {&slots_, &parked_})
+      for (Slot& s : *list)
+        if (s.ptr == p) {
+          s.lent = false;
+          return;
+        }
+    give_back(Slot{dev, stream, p, bytes, 0, false});
+  }
+
+  size_t kept_bytes() const { return kept_; }
+  size_t kept_slots() const { return slots_.size(); }
+  size_t parked() const { return parked_.size(); }
+  Alloc& allocator() { return alloc_; }
+
+ private:
+  struct Slot {
+    int dev;
+    void* stream;
+    void* ptr;
+    size_t bytes;
+    int small;  // calls in a row that needed an eighth or less
+    bool lent;
+  };
+  static size_t rounded(size_t bytes) {
+    size_t w = kMinBytes;
+    while (w < bytes) w *= 2;
+    return w;
+  }
+  Slot* find(int dev, const void* stream) {
+    for (Slot& s : slots_)
+      if (s.dev == dev && s.stream == stream) return &s;
+    return nullptr;
+  }
+  void give_back(Slot s) {
+    s.lent = false;
+    if (!alloc_.free(s.dev, s.stream, s.ptr)) parked_.push_back(s);
+  }
+
+  Alloc alloc_;
+  std::mutex mu_;
+  std::vector<Slot> slots_;
+  std::vector<Slot> parked_;
+  size_t kept_ = 0;
+};
+
+}  // namespace bitonic
