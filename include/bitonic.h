@@ -201,17 +201,29 @@ int bitonic_validation_error(int32_t* code);
  * 2^31 (2^31 where the allocation is unknown).  Host-side; nothing is
  * enqueued.  -1 for a NULL pointer or another key size.  The merge phases
  * enqueued are those up to ceil(log2 bound) (bitonic_plan_shapes with a
- * segmented layout and n = bound lists the launches).
+ * segmented layout and n = bound lists the launches), or up to 2^17 where
+ * longer segments go by digits.
  */
 int64_t bitonic_segmented_default_bound(const void* keys, int key_bytes);
 
 /*
+ * Segments of more than 2^13 elements go by their digits, as long single
+ * arrays do, when the longest has more than 2^17 (with a bound: when the
+ * bound is above that; without one: in allocations of more than 2^20 4-byte
+ * or 2^22 8-byte elements).  The workspace, as of a single array as long as all
+ * segments together, is laid out for the smaller of nseg * max_seg_len and
+ * the elements from `keys` to the end of their allocation, by the runtime's
+ * records; where that is more than 2^28 elements, or cannot be had, the
+ * network sorts them.  (bitonic_sort_segmented_noalloc_i32 and graphs always
+ * run the network.)
+ *
  * As bitonic_sort_segmented_i32, with a host-side bound: every segment holds
  * at most max_seg_len keys (0 = unknown: then the bound of
  * bitonic_sort_segmented_i32 is taken).  The bound fixes how many merge
  * phases are enqueued; a segment longer than the bound is undefined
  * behaviour.  Launches: a prep kernel, one persistent kernel for all segments
- * of up to 2^13 keys, and, if the bound exceeds 2^13, one tile-sort launch
+ * of up to 2^13 keys, and, if the bound exceeds 2^13, those of the digit sort
+ * (one per digit and two) or, by the network, one tile-sort launch
  * plus, per phase p = 14 .. ceil(log2 bound), its fused long-stride passes
  * (at most "seg_fuse" steps each, default 5) and one tile merge.  Like
  * bitonic_sort_segmented_i32 it refuses a capturing stream.
@@ -406,7 +418,8 @@ int64_t bitonic_plan_describe(int64_t n, const bitonic_plan* plan, int32_t* kind
  * 16-byte boundary), BITONIC_LAYOUT_KEYS64, BITONIC_LAYOUT_PAIRS, and the
  * segmented sorts BITONIC_LAYOUT_SEG_KEYS32, BITONIC_LAYOUT_SEG_PAIRS,
  * BITONIC_LAYOUT_SEG_KEYS64, whose longest segment holds n elements (the
- * bound of bitonic_sort_segmented_bounded_i32).  Returns the number of
+ * bound of bitonic_sort_segmented_bounded_i32).  The network's launches, for
+ * sizes that go by digits too.  Returns the number of
  * launches, or -1 for a bad argument (n < 0, n > 2^31, a bad plan or layout).
  */
 typedef struct bitonic_launch_shape {

@@ -40,24 +40,10 @@ __global__ __launch_bounds__(1024) void radix_scan_kernel(const uint32_t* __rest
   const bool value_pass = pairs && pass < sizeof(int32_t) * 8 / kRadixBits;
   if (value_pass && tid < blocks && unordered[tid]) down = 1;
   __syncthreads();
-  uint32_t t = 0, incl = 0;
-  if (g == 0) {
-    t = sums[0][d] + sums[1][d] + sums[2][d] + sums[3][d];
-    if (t == n) one_digit = 1;
-    incl = t;
-    const uint32_t lane = tid & 63u;
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = __shfl_up(incl, o);
-      if (lane >= (uint32_t)o) incl += y;
-    }
-    if (lane == 63) wave_sum[tid >> 6] = incl;
-  }
-  __syncthreads();
-  if (g == 0) {
-    uint32_t before = 0;
-    for (uint32_t w = 0; w < (tid >> 6); ++w) before += wave_sum[w];
-    base[pass * kRadixBins + d] = before + incl - t;
-  }
+  const uint32_t t = g == 0 ? sums[0][d] + sums[1][d] + sums[2][d] + sums[3][d] : 0u;
+  if (g == 0 && t == n) one_digit = 1;
+  const uint32_t before = radix_scan_bins(t, g == 0, tid >> 6, wave_sum);
+  if (g == 0) base[pass * kRadixBins + d] = before;
   if (tid == 0) meta->trivial[pass] = one_digit || (value_pass && !down) ? 1u : 0u;
 }
 

@@ -77,13 +77,15 @@ __global__ __launch_bounds__(1024) void seg_prep_kernel(const int64_t* __restric
                                                         uint32_t* __restrict__ big_ids,
                                                         uint64_t* __restrict__ big_keys,
                                                         uint64_t* __restrict__ big_tiles,
-                                                        int tile_log, int validated) {
+                                                        int tile_log, int validated, int radix_cls,
+                                                        uint32_t* __restrict__ any_unordered) {
   __shared__ uint32_t cnt[32];
   __shared__ uint32_t cur[32];
   __shared__ uint64_t part_k[1024];
   __shared__ uint64_t part_t[1024];
   __shared__ uint32_t nbig_s;
   const uint32_t tid = threadIdx.x;
+  if (tid == 0 && any_unordered) *any_unordered = 0;
   if (validated && meta->invalid) {
     // a refused table classifies as empty: no kernel after this one touches
     // the keys or reads the offsets again
@@ -91,6 +93,7 @@ __global__ __launch_bounds__(1024) void seg_prep_kernel(const int64_t* __restric
       meta->small_counter = 0;
       meta->small_items = 0;
       meta->nbig = 0;
+      meta->nradix = 0;
       meta->max_class = 0;
       for (int i = 0; i < kSmallClasses; ++i) {
         meta->small_start[i] = 0;
@@ -141,6 +144,10 @@ __global__ __launch_bounds__(1024) void seg_prep_kernel(const int64_t* __restric
     }
     for (int c = 0; c <= kSegSmallMaxLog2; ++c) meta->big_ge[c] = bpos;
     meta->big_ge[32] = 0;
+    const bool radix = radix_cls != 0 && maxc >= radix_cls;
+    meta->nradix = radix ? bpos : 0;
+    if (radix)
+      for (int c = 0; c < 32; ++c) meta->big_ge[c] = 0;
     meta->nbig = bpos;
     meta->max_class = maxc;
     nbig_s = bpos;
@@ -213,9 +220,10 @@ static void seg_dispatch(const SegData& d, const SegLaunch& l, const int64_t* of
 }
 
 void launch_seg_prep(const int64_t* offsets, int64_t nseg, const SegScratch& sc, int tile_log,
-                     bool validated, hipStream_t st) {
+                     bool validated, int radix_cls, uint32_t* any_unordered, hipStream_t st) {
   seg_prep_kernel<<<1, 1024, 0, st>>>(offsets, nseg, sc.meta, sc.small_ids, sc.big_ids,
-                                      sc.big_keys, sc.big_tiles, tile_log, validated ? 1 : 0);
+                                      sc.big_keys, sc.big_tiles, tile_log, validated ? 1 : 0,
+                                      radix_cls, any_unordered);
 }
 
 void launch_seg_small(const SegData& d, const int64_t* offsets, const SegScratch& sc, int grid,

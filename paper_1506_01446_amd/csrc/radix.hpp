@@ -51,19 +51,15 @@ constexpr int radix_items(int64_t n, int elem_bytes) {
   return most / 4;
 }
 
-// Tiles per group, groups per supergroup of a pass's prefix sums, and the
-// rows of kRadixBins words that hold them: the tiles' counts, the groups'
-// sums, the supergroups' sums, and the counts ahead of each supergroup.
+// Tiles per group and groups per supergroup of a pass's prefix sums, and the
+// most rows of kRadixBins words that they take for `arrays` arrays of
+// `tiles` tiles in all: the tiles' counts, the groups' sums, the
+// supergroups' sums, and the counts ahead of each supergroup.
 constexpr uint32_t kRadixGroupLog = 4;
 constexpr uint32_t kRadixGroup = 1u << kRadixGroupLog;
-__host__ __device__ constexpr uint32_t radix_groups(uint32_t tiles) {
-  return (tiles + kRadixGroup - 1) >> kRadixGroupLog;
-}
-__host__ __device__ constexpr uint32_t radix_supers(uint32_t tiles) {
-  return (tiles + kRadixGroup * kRadixGroup - 1) >> (2 * kRadixGroupLog);
-}
-__host__ __device__ constexpr uint32_t radix_state_rows(uint32_t tiles) {
-  return tiles + radix_groups(tiles) + 2 * radix_supers(tiles);
+__host__ __device__ constexpr uint32_t radix_state_rows(uint32_t tiles, uint32_t arrays) {
+  return tiles + (tiles >> kRadixGroupLog) + arrays +
+         2 * ((tiles >> (2 * kRadixGroupLog)) + arrays);
 }
 
 // Layout of the workspace.
@@ -92,7 +88,7 @@ inline size_t radix_space(char* p, uint32_t n, int elem_bytes, RadixSpace* s) {
   const size_t row = kRadixBins * sizeof(uint32_t);
   const size_t passes = (size_t)elem_bytes;
   const size_t blocks = radix_hist_blocks(n);
-  const size_t states = radix_state_rows(radix_tiles(n, elem_bytes)) * row;
+  const size_t states = radix_state_rows(radix_tiles(n, elem_bytes), 1) * row;
   size_t at = 0;
   auto take = [&](size_t bytes) {
     char* const q = p + at;

@@ -50,39 +50,40 @@ constexpr int radix_passes() {
 
 constexpr int kRadixHistThreads = 512;
 
-// Counts every digit of the workgroup's contiguous share.  A bin is kept in
-// 64 / passes copies (64 KiB of LDS in all, two workgroups per CU), lane l
-// adding to copy l mod copies: an array whose digits are all alike then adds
-// at most `passes` times in turn to one word per wave, and not 64 times.
-template <bool FL, class ST, class CD>
-__global__ __launch_bounds__(kRadixHistThreads) void radix_hist_kernel(
-    ST a, uint32_t n, CD cd, RadixMeta* __restrict__ meta, uint32_t* __restrict__ partial,
-    uint32_t* __restrict__ unordered, uint32_t* __restrict__ state, uint32_t state_words) {
+// LDS of a counting workgroup.  A bin is kept in 64 / passes copies (64 KiB
+// in all, two workgroups per CU), lane l adding to copy l mod copies: an
+// array whose digits are all alike then adds at most `passes` times in turn
+// to one word per wave, and not 64 times.
+template <class ST>
+struct RadixBinsLds {
+  static constexpr int P = radix_passes<ST>();
+  static constexpr int C = 64 / P;
+  uint32_t bins[P * kRadixBins * C];
+  uint32_t decrease;
+};
+
+// Counts every digit of elements lo .. hi of a (n in all) with the whole
+// workgroup; then bin b's count (pass b / 256, digit b mod 256) is
+// radix_bin_count(lds, b), and lds.decrease is 1 if a pair's value (Pairs) is
+// above the next one's.
+template <class MAP, class ST>
+__device__ __forceinline__ void radix_count(RadixBinsLds<ST>& lds, const MAP& map, const ST& a,
+                                            uint64_t lo, uint64_t hi, uint64_t n) {
   using E = typename ST::E;
-  constexpr int P = radix_passes<ST>();
-  constexpr int C = 64 / P;
+  using L = RadixBinsLds<ST>;
   constexpr uint32_t NT = kRadixHistThreads;
-  __shared__ uint32_t bins[P * kRadixBins * C];
-  __shared__ uint32_t decrease;
-  const RadixMap<ST, FL, CD> map{cd};
   const uint32_t tid = threadIdx.x;
-  for (uint32_t i = tid; i < P * kRadixBins * C; i += NT) bins[i] = 0;
-  if (tid == 0) decrease = 0;
-  // the first executed pass's prefix sums, and every pass's ticket
-  for (uint32_t i = blockIdx.x * NT + tid; i < state_words; i += gridDim.x * NT) state[i] = 0;
-  if (blockIdx.x == 0 && tid < kRadixMaxPasses) meta->ticket[tid] = 0;
+  for (uint32_t i = tid; i < L::P * kRadixBins * L::C; i += NT) lds.bins[i] = 0;
+  if (tid == 0) lds.decrease = 0;
   __syncthreads();
-  const uint32_t copy = tid % C;
+  const uint32_t copy = tid % L::C;
   auto count = [&](E x) {
     const auto u = map.enc(x);
-    static_for<0, P>([&](auto p) {
+    static_for<0, L::P>([&](auto p) {
       const uint32_t d = (uint32_t)(u >> (kRadixBits * (int)p)) & (kRadixBins - 1);
-      atomicAdd(&bins[((int)p * kRadixBins + d) * C + copy], 1u);
+      atomicAdd(&lds.bins[((int)p * kRadixBins + d) * L::C + copy], 1u);
     });
   };
-  const uint32_t per = ((n - 1) / gridDim.x / NT + 1) * NT;
-  const uint64_t lo = (uint64_t)blockIdx.x * per;
-  const uint64_t hi = lo + per < n ? lo + per : n;
   constexpr int U = 8;
   uint64_t i = lo + tid;
   for (; i + (U - 1) * NT < hi; i += U * NT) {
@@ -95,15 +96,59 @@ __global__ __launch_bounds__(kRadixHistThreads) void radix_hist_kernel(
     bool down = false;
     for (uint64_t j = lo + tid; j < hi; j += NT)
       down = down || (j + 1 < n && a.v[j] > a.v[j + 1]);
-    if (down) decrease = 1;
+    if (down) lds.decrease = 1;
   }
   __syncthreads();
-  for (uint32_t b = tid; b < P * kRadixBins; b += NT) {
-    uint32_t s = 0;
-    static_for<0, C>([&](auto k) { s += bins[b * C + (k + tid) % C]; });
-    partial[(size_t)blockIdx.x * (P * kRadixBins) + b] = s;
+}
+
+template <class ST>
+__device__ __forceinline__ uint32_t radix_bin_count(const RadixBinsLds<ST>& lds, uint32_t b) {
+  uint32_t s = 0;
+  static_for<0, RadixBinsLds<ST>::C>([&](auto k) {
+    s += lds.bins[b * RadixBinsLds<ST>::C + (k + threadIdx.x) % RadixBinsLds<ST>::C];
+  });
+  return s;
+}
+
+// Each workgroup counts a contiguous share of the array.
+template <bool FL, class ST, class CD>
+__global__ __launch_bounds__(kRadixHistThreads) void radix_hist_kernel(
+    ST a, uint32_t n, CD cd, RadixMeta* __restrict__ meta, uint32_t* __restrict__ partial,
+    uint32_t* __restrict__ unordered, uint32_t* __restrict__ state, uint32_t state_words) {
+  constexpr int P = radix_passes<ST>();
+  constexpr uint32_t NT = kRadixHistThreads;
+  __shared__ RadixBinsLds<ST> lds;
+  const uint32_t tid = threadIdx.x;
+  // the first executed pass's prefix sums, and every pass's ticket
+  for (uint32_t i = blockIdx.x * NT + tid; i < state_words; i += gridDim.x * NT) state[i] = 0;
+  if (blockIdx.x == 0 && tid < kRadixMaxPasses) meta->ticket[tid] = 0;
+  const uint32_t per = ((n - 1) / gridDim.x / NT + 1) * NT;
+  const uint64_t lo = (uint64_t)blockIdx.x * per;
+  const uint64_t hi = lo + per < n ? lo + per : n;
+  radix_count(lds, RadixMap<ST, FL, CD>{cd}, a, lo, hi, n);
+  for (uint32_t b = tid; b < P * kRadixBins; b += NT)
+    partial[(size_t)blockIdx.x * (P * kRadixBins) + b] = radix_bin_count(lds, b);
+  if (tid == 0) unordered[blockIdx.x] = lds.decrease;
+}
+
+// With 256 consecutive threads (four waves, wave_sum of four words): the sum
+// of the smaller digits' counts.  Every thread of the workgroup calls it;
+// `in` says whether the thread is one of the 256, `four` its wave among them.
+__device__ __forceinline__ uint32_t radix_scan_bins(uint32_t count, bool in, uint32_t four,
+                                                    uint32_t* wave_sum) {
+  const uint32_t lane = threadIdx.x & 63u;
+  uint32_t incl = count;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(incl, o);
+    if (lane >= (uint32_t)o) incl += y;
   }
-  if (tid == 0) unordered[blockIdx.x] = decrease;
+  if (in && lane == 63) wave_sum[four] = incl;
+  __syncthreads();
+  uint32_t before = incl - count;
+  if (in)
+    for (uint32_t w = 0; w < four; ++w) before += wave_sum[w];
+  __syncthreads();
+  return before;
 }
 
 // ---------------------------------------------------------------------------
@@ -157,11 +202,69 @@ __device__ __forceinline__ uint32_t radix_state_sum(const uint32_t* p, uint32_t 
   return sum;
 }
 
-// The pass on digit `pass` of the elements: from a to b after an even number
-// of executed passes, else from b to a.
+// Trivial passes are left out, an even number of them, so that the last
+// executed pass writes the caller's array.  False if pass is one of them;
+// else *odd says whether an odd number of passes ran before it.
+template <int P>
+__device__ __forceinline__ bool radix_executes(const uint32_t* trivial, int pass, bool* odd) {
+  int leave = 0;
+  static_for<0, P>([&](auto p) { leave += (int)trivial[p]; });
+  leave &= ~1;
+  int executed = 0;
+  bool skip = false;
+  for (int p = 0; p <= pass; ++p) {
+    executed += p > 0 && !skip;
+    skip = leave > 0 && trivial[p] != 0;
+    leave -= skip;
+  }
+  *odd = (executed & 1) != 0;
+  return !skip;
+}
+
+// Where the prefix sums of an array's pass are: rows of 256 words for its
+// tiles, their groups, their supergroups, and what is ahead of those.
+struct RadixRows {
+  uint32_t* tiles;
+  uint32_t* groups;
+  uint32_t* supers;
+  uint32_t* ahead;
+};
+
+// The rows of an array whose first tile is `first` of the sort's `tiles`
+// tiles, behind `arrays` arrays before it: every array begins its groups and
+// supergroups with rows of its own (sum of ceil(t / 16) over them is at most
+// first / 16 + arrays).
+__device__ __forceinline__ RadixRows radix_rows(uint32_t* state, uint32_t tiles, uint32_t narrays,
+                                                uint32_t first, uint32_t arrays) {
+  const size_t g = (size_t)tiles + (first >> kRadixGroupLog) + arrays;
+  const size_t g_rows = (size_t)(tiles >> kRadixGroupLog) + narrays;
+  const size_t s_rows = (size_t)(tiles >> (2 * kRadixGroupLog)) + narrays;
+  const size_t s = (size_t)tiles + g_rows + (first >> (2 * kRadixGroupLog)) + arrays;
+  return RadixRows{state + (size_t)first * kRadixBins, state + g * kRadixBins,
+                   state + s * kRadixBins, state + (s + s_rows) * kRadixBins};
+}
+
+// LDS of a pass's workgroup.
+template <class U, int IPT>
+struct RadixLds {
+  static constexpr uint32_t NT = kRadixThreads;
+  static constexpr int NW = NT / 64;
+  static constexpr size_t TILE = (size_t)NT * IPT * sizeof(U);
+  static constexpr size_t HIST = (size_t)NW * kRadixBins * 4;
+  // the waves' digit counts, and then the tile in order of its digit
+  alignas(16) char shared[TILE > HIST ? TILE : HIST];
+  uint32_t part[2][kRadixBins];
+  uint32_t shift_of[kRadixBins];  // output index minus tile position, per digit
+  uint32_t wave_sum[kRadixBins / 64];
+  uint32_t tile;
+};
+
+// One tile of a pass on the digit at bit `shift`: tile `tile` of an array,
+// its elements src.get(0 .. valid), written to their places in dst (the
+// output array's start).  base: where each digit begins in the output.
 //
-// A workgroup takes the next tile from a ticket, so every tile before its own
-// is already being worked on; what it waits for below are the counts of those
+// The caller takes tiles from a ticket, so every tile before this one is
+// already being worked on; what is waited for below are the counts of those
 // tiles, which each publishes without waiting for anything, and (in the
 // first tile of a supergroup) the sums ahead of the supergroup before, which
 // wait for earlier tiles only.  So the wait ends whatever else runs on the
@@ -169,83 +272,52 @@ __device__ __forceinline__ uint32_t radix_state_sum(const uint32_t* p, uint32_t 
 //
 // The tile's digits are counted before they are ranked: the counts are on
 // their way to the tiles behind while this one does the ranking, its longest
-// part.
-template <bool FL, int IPT, class ST, class CD>
-__global__ __launch_bounds__(kRadixThreads, 8) void radix_pass_kernel(
-    ST a, ST b, uint32_t n, CD cd, int pass, RadixMeta* __restrict__ meta,
-    const uint32_t* __restrict__ base, uint32_t* __restrict__ state_a,
-    uint32_t* __restrict__ state_b) {
-  using MAP = RadixMap<ST, FL, CD>;
+// part.  The ranking's ballots bound the pass (61 % VALU busy at 2^24 4-byte
+// keys, 46 us against 19 us for a copy of the keys): about 70 VALU
+// instructions per element, 32 of them the ballots' masks.
+template <int IPT, class ST, class MAP>
+__device__ __forceinline__ void radix_tile(RadixLds<typename MAP::U, IPT>& lds, const MAP& map,
+                                           const ST& src, const ST& dst, uint32_t valid,
+                                           uint32_t tile, int shift, const uint32_t* base,
+                                           const RadixRows& rows, const RadixRows& clear) {
   using U = typename MAP::U;
-  constexpr int P = radix_passes<ST>();
   constexpr uint32_t NT = kRadixThreads;
   constexpr int NW = NT / 64;
   constexpr uint32_t T = NT * IPT;
   constexpr uint32_t BINS = kRadixBins;
-  // the waves' digit counts, and then the tile in order of its digit
-  constexpr size_t LDS = T * sizeof(U) > NW * BINS * 4 ? T * sizeof(U) : NW * BINS * 4;
-  __shared__ __attribute__((aligned(16))) char lds[LDS];
-  __shared__ uint32_t part[2][BINS];
-  __shared__ uint32_t shift_of[BINS];  // output index minus tile position, per digit
-  __shared__ uint32_t wave_sum[BINS / 64];
-  __shared__ uint32_t tile_s;
-  U* const exch = reinterpret_cast<U*>(lds);
-  uint32_t (*const whist)[BINS] = reinterpret_cast<uint32_t (*)[BINS]>(lds);
-  const MAP map{cd};
-
-  // Trivial passes are left out, an even number of them, so that the last
-  // executed pass writes the caller's array.
-  int leave = 0;
-  static_for<0, P>([&](auto p) { leave += (int)meta->trivial[p]; });
-  leave &= ~1;
-  int executed = 0;
-  bool skip = false;
-  for (int p = 0; p <= pass; ++p) {
-    executed += p > 0 && !skip;
-    skip = leave > 0 && meta->trivial[p] != 0;
-    leave -= skip;
-  }
-  if (skip) return;
-  const bool odd = (executed & 1) != 0;
-  const ST src = odd ? b : a;
-  const ST dst = odd ? a : b;
-  const uint32_t tiles = gridDim.x;
-  uint32_t* const state = odd ? state_b : state_a;
-  uint32_t* const next_state = odd ? state_a : state_b;
-  uint32_t* const groups = state + (size_t)tiles * BINS;
-  uint32_t* const supers = groups + (size_t)radix_groups(tiles) * BINS;
-  uint32_t* const ahead = supers + (size_t)radix_supers(tiles) * BINS;
-  const int shift = pass * kRadixBits;
+  U* const exch = reinterpret_cast<U*>(lds.shared);
+  uint32_t (*const whist)[BINS] = reinterpret_cast<uint32_t (*)[BINS]>(lds.shared);
   auto digit = [&](U u) { return (uint32_t)(u >> shift) & (BINS - 1); };
-
   const uint32_t tid = threadIdx.x;
   const uint32_t lane = tid & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (tid == 0) tile_s = atomicAdd(&meta->ticket[pass], 1u);
-  for (uint32_t i = tid; i < NW * BINS; i += NT) (&whist[0][0])[i] = 0;
-  __syncthreads();
-  const uint32_t tile = __builtin_amdgcn_readfirstlane(tile_s);
-  const uint32_t t0 = tile * T;
-  const uint32_t valid = n - t0 < T ? n - t0 : T;
   const uint32_t super = tile >> (2 * kRadixGroupLog), group = tile >> kRadixGroupLog;
   const uint32_t in_group = tile & (kRadixGroup - 1), in_super = group & (kRadixGroup - 1);
 
+  for (uint32_t i = tid; i < NW * BINS; i += NT) (&whist[0][0])[i] = 0;
   // Items of a wave are 64 consecutive elements each.  Past the end of the
   // array the largest element stands in: it ranks behind the real ones of
   // its digit, the last.
   U x[IPT];
   const uint32_t first = wave * (64u * IPT) + lane;
-  const ST s = src.at(t0);
   if (valid == T) {
-    static_for<0, IPT>([&](auto I) { x[I] = (U)s.getb((first + 64u * I) * ST::kUnit); });
+    static_for<0, IPT>([&](auto I) { x[I] = (U)src.getb((first + 64u * I) * ST::kUnit); });
     static_for<0, IPT>([&](auto I) { x[I] = map.enc((typename ST::E)x[I]); });
   } else {
     static_for<0, IPT>([&](auto I) {
-      x[I] = first + 64u * I < valid ? map.enc(s.get(first + 64u * I)) : ~(U)0;
+      x[I] = first + 64u * I < valid ? map.enc(src.get(first + 64u * I)) : ~(U)0;
     });
   }
-  for (uint32_t r = tile; r < radix_state_rows(tiles); r += tiles)
-    if (tid < BINS) next_state[(size_t)r * BINS + tid] = 0;
+  // this tile's rows of the next executed pass
+  if (tid < BINS) {
+    clear.tiles[(size_t)tile * BINS + tid] = 0;
+    if (in_group == 0) clear.groups[(size_t)group * BINS + tid] = 0;
+    if (in_group == 0 && in_super == 0) {
+      clear.supers[(size_t)super * BINS + tid] = 0;
+      clear.ahead[(size_t)super * BINS + tid] = 0;
+    }
+  }
+  __syncthreads();
 
   uint32_t* const wh = whist[wave];
   U differ = 0;
@@ -264,21 +336,21 @@ __global__ __launch_bounds__(kRadixThreads, 8) void radix_pass_kernel(
   if (tid < BINS) {
     static_for<0, NW>([&](auto w) { total += whist[w][tid]; });
     const uint32_t real = tid == BINS - 1 ? total - (T - valid) : total;
-    radix_state_put(state + (size_t)tile * BINS + tid, kRadixReady | real);
-    radix_state_add(groups + (size_t)group * BINS + tid, kRadixGroupOne | real);
-    radix_state_add(supers + (size_t)super * BINS + tid, kRadixSuperOne | real);
+    radix_state_put(rows.tiles + (size_t)tile * BINS + tid, kRadixReady | real);
+    radix_state_add(rows.groups + (size_t)group * BINS + tid, kRadixGroupOne | real);
+    radix_state_add(rows.supers + (size_t)super * BINS + tid, kRadixSuperOne | real);
     incl = total;
     for (int o = 1; o < 64; o <<= 1) {
       const uint32_t y = __shfl_up(incl, o);
       if (lane >= (uint32_t)o) incl += y;
     }
-    if (lane == 63) wave_sum[wave] = incl;
+    if (lane == 63) lds.wave_sum[wave] = incl;
   }
   __syncthreads();
   if (tid < BINS) {
     // where each digit begins in the tile, then where each wave's share does
     uint32_t before = 0;
-    for (uint32_t w = 0; w < wave; ++w) before += wave_sum[w];
+    for (uint32_t w = 0; w < wave; ++w) before += lds.wave_sum[w];
     excl = before + incl - total;
     uint32_t run = excl;
     static_for<0, NW>([&](auto w) {
@@ -319,29 +391,30 @@ __global__ __launch_bounds__(kRadixThreads, 8) void radix_pass_kernel(
   // the elements of each digit ahead of this tile's
   const uint32_t d = tid & (BINS - 1);
   if (wave < BINS / 64) {
-    part[0][d] =
-        radix_state_sum<kRadixReady, 1>(state + (size_t)(tile - in_group) * BINS + d, in_group) -
+    lds.part[0][d] =
+        radix_state_sum<kRadixReady, 1>(rows.tiles + (size_t)(tile - in_group) * BINS + d,
+                                        in_group) -
         excl;
   } else if (wave < 2 * BINS / 64) {
     uint32_t start;
     if (super == 0) {
-      start = base[pass * BINS + d];
+      start = base[d];
     } else {
-      start = radix_state_sum<kRadixReady, 1>(ahead + (size_t)(super - 1) * BINS + d, 1);
+      start = radix_state_sum<kRadixReady, 1>(rows.ahead + (size_t)(super - 1) * BINS + d, 1);
       start += radix_state_sum<kRadixSuperOne, kRadixGroup * kRadixGroup>(
-          supers + (size_t)(super - 1) * BINS + d, 1);
+          rows.supers + (size_t)(super - 1) * BINS + d, 1);
     }
     if (in_group == 0 && in_super == 0)
-      radix_state_put(ahead + (size_t)super * BINS + d, kRadixReady | start);
-    part[1][d] = start + radix_state_sum<kRadixGroupOne, kRadixGroup>(
-                             groups + (size_t)(group - in_super) * BINS + d, in_super);
+      radix_state_put(rows.ahead + (size_t)super * BINS + d, kRadixReady | start);
+    lds.part[1][d] = start + radix_state_sum<kRadixGroupOne, kRadixGroup>(
+                                 rows.groups + (size_t)(group - in_super) * BINS + d, in_super);
   }
   __syncthreads();
-  if (tid < BINS) shift_of[tid] = part[0][tid] + part[1][tid];
+  if (tid < BINS) lds.shift_of[tid] = lds.part[0][tid] + lds.part[1][tid];
   __syncthreads();
   auto put = [&](uint32_t i) {
     const U u = exch[i];
-    dst.put(shift_of[digit(u)] + i, map.dec(u));
+    dst.put(lds.shift_of[digit(u)] + i, map.dec(u));
   };
   if (valid == T) {
     static_for<0, IPT>([&](auto I) { put((uint32_t)I * NT + tid); });
@@ -350,6 +423,30 @@ __global__ __launch_bounds__(kRadixThreads, 8) void radix_pass_kernel(
       if ((uint32_t)I * NT + tid < valid) put((uint32_t)I * NT + tid);
     });
   }
+}
+
+// The pass on digit `pass` of the elements: from a to b after an even number
+// of executed passes, else from b to a.  One workgroup per tile.
+template <bool FL, int IPT, class ST, class CD>
+__global__ __launch_bounds__(kRadixThreads, 8) void radix_pass_kernel(
+    ST a, ST b, uint32_t n, CD cd, int pass, RadixMeta* __restrict__ meta,
+    const uint32_t* __restrict__ base, uint32_t* __restrict__ state_a,
+    uint32_t* __restrict__ state_b) {
+  using MAP = RadixMap<ST, FL, CD>;
+  constexpr uint32_t T = kRadixThreads * IPT;
+  __shared__ RadixLds<typename MAP::U, IPT> lds;
+  bool odd;
+  if (!radix_executes<radix_passes<ST>()>(meta->trivial, pass, &odd)) return;
+  if (threadIdx.x == 0) lds.tile = atomicAdd(&meta->ticket[pass], 1u);
+  __syncthreads();
+  const uint32_t tile = __builtin_amdgcn_readfirstlane(lds.tile);
+  const uint32_t t0 = tile * T;
+  const ST src = odd ? b : a;
+  const ST dst = odd ? a : b;
+  radix_tile<IPT>(lds, MAP{cd}, src.at(t0), dst, n - t0 < T ? n - t0 : T, tile,
+                  pass * kRadixBits, base + pass * kRadixBins,
+                  radix_rows(odd ? state_b : state_a, gridDim.x, 1, 0, 0),
+                  radix_rows(odd ? state_a : state_b, gridDim.x, 1, 0, 0));
 }
 
 // ---------------------------------------------------------------------------
@@ -361,7 +458,7 @@ static void radix_run_items(ST a, ST b, CD cd, uint32_t n, const RadixSpace& s, 
   constexpr uint32_t T = kRadixThreads * IPT;
   const uint32_t tiles = n / T + (n % T != 0);
   radix_hist_kernel<FL><<<radix_hist_blocks(n), kRadixHistThreads, 0, st>>>(
-      a, n, cd, s.meta, s.partial, s.unordered, s.state[0], radix_state_rows(tiles) * kRadixBins);
+      a, n, cd, s.meta, s.partial, s.unordered, s.state[0], radix_state_rows(tiles, 1) * kRadixBins);
   launch_radix_scan(s, n, P, std::is_same_v<ST, Pairs>, st);
   for (int p = 0; p < P; ++p)
     radix_pass_kernel<FL, IPT><<<tiles, kRadixThreads, 0, st>>>(a, b, n, cd, p, s.meta, s.base,

@@ -171,3 +171,95 @@ def test_threads_and_streams():
     for t in range(4):
         for i in range(len(sizes)):
             assert np.array_equal(got[t][i].cpu().numpy(), O.sort_i32(keys[t][i], True)), (t, i)
+
+
+# Segmented sorts: the big segments go by digits when the longest has more
+# than 2^17 elements.  Lengths around the small segments' limit (2^13), the
+# tiles (2^14, 2^13), a group (16 tiles) and a supergroup (256 tiles: 2^21
+# 8-byte elements), with empty segments between.
+SEG_LENS = [
+    [(1 << 17) + 1, 0, 8193, 5, 8192, 1 << 14, (1 << 14) + 1, 70_001],
+    [1 << 18, 1, (1 << 18) + 1, 3 * 8192, 300, 0, 150_000],
+    [(1 << 21) + 8193, 20_000, 1 << 17],
+]
+
+
+def _segments(lens, lead):
+    off = np.zeros(len(lens) + 1, dtype=np.int64)
+    np.cumsum(lens, out=off[1:])
+    return off + lead
+
+
+def _oracle_segments(sort, k, off):
+    out = k.copy()
+    for a, b in zip(off[:-1], off[1:]):
+        out[a:b] = sort(k[a:b])
+    return out
+
+
+@pytest.mark.parametrize("lens", SEG_LENS, ids=["classes", "tiles", "supergroup"])
+@pytest.mark.parametrize("bounded", [True, False])
+def test_segments(lens, bounded):
+    B = _bind()
+    off = _segments(lens, 3)      # segments start off a 16-byte boundary
+    n = int(off[-1]) + 5
+    ot = torch.from_numpy(off).cuda()
+    for i, type_ in enumerate(["int32", "uint32", "float32", "int64", "uint64", "float64"]):
+        asc = i % 2 == 0
+        w = _words(KINDS[(i + len(lens)) % 6], n, 70 + i)
+        k = w.copy() if i >= 3 else w.astype(np.int32)
+        t = _gpu(k)
+        B.bitonic_sort_segmented_keys(t, ot, asc, type_, max(lens) if bounded else 0)
+        sort = (lambda a: O.sort_keys64(a.view(type_), i, asc).view(np.int64)) if i >= 3 else \
+            (lambda a: O.sort_keys(a.view(type_), i, asc).view(np.int32))
+        assert np.array_equal(t.cpu().numpy(), _oracle_segments(sort, k, off)), (type_, asc)
+
+
+@pytest.mark.parametrize("lens", SEG_LENS, ids=["classes", "tiles", "supergroup"])
+@pytest.mark.parametrize("values", ["index", "uniform", "mixed"])
+def test_segment_pairs(lens, values):
+    """Values in order in every segment, in none, and in every other one."""
+    B = _bind()
+    off = _segments(lens, 1)
+    n = int(off[-1]) + 2
+    k = _words("few", n, 31).astype(np.int32)
+    v = W.uniform_i32(77, n)
+    for s, (a, b) in enumerate(zip(off[:-1], off[1:])):
+        if values == "index" or (values == "mixed" and s % 2 == 0):
+            v[a:b] = np.arange(b - a, dtype=np.int32)
+    kt, vt = _gpu(k), _gpu(v)
+    B.bitonic_sort_segmented_pairs(kt, vt, torch.from_numpy(off).cuda(), False, "int32", max(lens))
+    wk, wv = k.copy(), v.copy()
+    for a, b in zip(off[:-1], off[1:]):
+        wk[a:b], wv[a:b] = O.sort_pairs(k[a:b], v[a:b], 0, False)
+    assert np.array_equal(kt.cpu().numpy(), wk)
+    assert np.array_equal(vt.cpu().numpy(), wv)
+
+
+def test_segments_without_a_bound_stay_with_the_network_below_its_limit():
+    """No bound and no segment above 2^17 elements: the device leaves the big
+    segments to the network's kernels."""
+    B = _bind()
+    lens = [1 << 17, 9000, 40_000, 100, (1 << 16) + 1]
+    off = _segments(lens, 0)
+    k = W.uniform_i32(3, int(off[-1]) + (1 << 21))   # the bound is the allocation's
+    t = _gpu(k)
+    B.bitonic_sort_segmented_i32(t, torch.from_numpy(off).cuda(), True)
+    assert np.array_equal(t.cpu().numpy(), _oracle_segments(O.sort_i32, k, off))
+
+
+@pytest.mark.parametrize("type_", ["int32", "float64"])
+def test_segment_beyond_the_workspace(type_):
+    """A segment with more elements than the workspace was laid out for (by
+    the caller's bound) is sorted where it is; nothing is written past the
+    workspace or the segment."""
+    B = _bind()
+    bound, n = (1 << 17) + 1, (1 << 17) + 300
+    w = _words("uniform", n + 9, 8)
+    k = w.astype(np.int32) if type_ == "int32" else w.copy()
+    t = _gpu(k)
+    B.bitonic_sort_segmented_keys(t, torch.tensor([0, n], device="cuda"), False, type_, bound)
+    want = k.copy()
+    want[:n] = O.sort_i32(k[:n], False) if type_ == "int32" else \
+        O.sort_keys64(k[:n].view(type_), 5, False).view(np.int64)
+    assert np.array_equal(t.cpu().numpy(), want)
