@@ -284,6 +284,17 @@ def bitonic_wide_plan_passes(n: int, plan=None) -> int:
     return int(load().bitonic_wide_plan_passes(int(n), _plan_ref(p)))
 
 
+def _segment_bound(keys, max_seg_len) -> int:
+    """The caller's bound on the segment length, or else the elements from
+    the tensor's first to the end of its storage: segments lie inside it, and
+    an allocator's blocks, whose size the library would take, are larger (by
+    2 to 20 MiB: up to ten merge phases that find no segment)."""
+    if max_seg_len or not keys.numel():
+        return int(max_seg_len or 0)
+    size = keys.element_size()
+    return min(keys.untyped_storage().nbytes() // size - keys.storage_offset(), 1 << 31)
+
+
 def bitonic_sort_segmented_pairs(keys, values, offsets, ascending: bool = True, key_type=None,
                                  max_seg_len: int | None = None, stream=None) -> None:
     """Sort (key, value) pairs per CSR segment: by key, equal keys by value
@@ -291,8 +302,9 @@ def bitonic_sort_segmented_pairs(keys, values, offsets, ascending: bool = True, 
     kp, vptr = _pair_ptrs(keys, values)
     op = _keys_ptr(offsets, "int64")
     nseg = max(offsets.numel() - 1, 0)
+    bound = _segment_bound(keys, max_seg_len)
     _check("bitonic_sort_segmented_pairs",
-           load().bitonic_sort_segmented_pairs(kp, vptr, op, nseg, int(max_seg_len or 0),
+           load().bitonic_sort_segmented_pairs(kp, vptr, op, nseg, bound,
                                                _key_type(keys, key_type), int(bool(ascending)),
                                                _stream(stream)))
 
@@ -301,19 +313,20 @@ def bitonic_sort_segmented_keys(keys, offsets, ascending: bool = True, key_type=
                                 max_seg_len: int = 0, stream=None) -> None:
     """Per-segment sort of keys of any type: 4-byte (int32, uint32, float32)
     or 8-byte (int64, uint64, float64), from the dtype or key_type."""
+    bound = _segment_bound(keys, max_seg_len)
     if keys.element_size() == 8:
         kp, kt = _any64_ptr(keys), _key_type64(keys, key_type)
         op = _keys_ptr(offsets, "int64")
         _check("bitonic_sort_segmented_keys",
                load().bitonic_sort_segmented_keys(kp, op, max(offsets.numel() - 1, 0),
-                                                  int(max_seg_len), kt, int(bool(ascending)),
+                                                  bound, kt, int(bool(ascending)),
                                                   _stream(stream)))
         return
     kp = _any32_ptr(keys)
     op = _keys_ptr(offsets, "int64")
     _check("bitonic_sort_segmented_keys",
            load().bitonic_sort_segmented_keys(kp, op, max(offsets.numel() - 1, 0),
-                                              int(max_seg_len), _key_type(keys, key_type),
+                                              bound, _key_type(keys, key_type),
                                               int(bool(ascending)), _stream(stream)))
 
 
@@ -342,15 +355,10 @@ def bitonic_sort_segmented_i32(keys, offsets, ascending: bool = True, stream=Non
     kp = _keys_ptr(keys)
     op = _keys_ptr(offsets, "int64")
     nseg = max(offsets.numel() - 1, 0)
-    if max_seg_len is None:
-        _check("bitonic_sort_segmented_i32",
-               load().bitonic_sort_segmented_i32(kp, op, nseg, int(bool(ascending)),
-                                                 _stream(stream)))
-    else:
-        _check("bitonic_sort_segmented_bounded_i32",
-               load().bitonic_sort_segmented_bounded_i32(kp, op, nseg, int(max_seg_len),
-                                                         int(bool(ascending)),
-                                                         _stream(stream)))
+    _check("bitonic_sort_segmented_bounded_i32",
+           load().bitonic_sort_segmented_bounded_i32(kp, op, nseg,
+                                                     _segment_bound(keys, max_seg_len),
+                                                     int(bool(ascending)), _stream(stream)))
 
 
 def bitonic_sort_segmented_noalloc_i32(keys, offsets, max_seg_len: int, ascending: bool = True,

@@ -1056,8 +1056,11 @@ static int sort_segmented(void* keys_v, int32_t* values, const int64_t* offsets,
   int dev = 0;
   int rc = current_device(&dev);
   if (rc) return rc;
-  const bool tight = max_seg_len != 0;
-  if (!tight) max_seg_len = allocation_bound(keys_v, wide_keys ? 8 : 4);
+  const int64_t available = allocation_bound(keys_v, wide_keys ? 8 : 4);
+  // a bound that several segments cannot all come near says little about
+  // them: it is then the size of the keys' memory, or as good as that
+  const bool tight = max_seg_len != 0 && (nseg == 1 || max_seg_len < available / 2);
+  if (max_seg_len == 0) max_seg_len = available;
   void* base = nullptr;
   rc = stream_scratch(dev, st, seg_scratch_bytes(nseg), &base);
   if (rc) return rc;
