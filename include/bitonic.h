@@ -17,9 +17,8 @@
  *    tensors); the caller owns them.  Sorting is in place.
  *  - The plain single-array sorts (bitonic_sort_i32, bitonic_sort_keys,
  *    bitonic_sort_keys64, bitonic_sort_pairs) run the network on short arrays
- *    and sort longer ones (4-byte keys: more than 2^16, or more than 2^15
- *    when n is not a power of two; 8-byte elements: more than 2^15) by their
- *    digits, least significant first, through a workspace of the array's own
+ *    and sort longer ones (more than 2^16 elements) by their digits, least
+ *    significant first, through a workspace of the array's own
  *    size.  The result is the same (it is unique).  They run the network at
  *    every size where the workspace cannot be allocated, on a stream that is
  *    being captured into a graph, and for n = 2^31.  The calls that take a
@@ -329,8 +328,8 @@ typedef struct bitonic_plan {
  * (elements per tile), its fuse 1..8 (7 and 8 split each column over two
  * or four lanes, for n a power of two and phases up to 29; otherwise at
  * most 6 are used); merge_blocks_per_cu is ignored (one tile per
- * workgroup).  Library choices (0): tile_log2 13, fuse 8 (tuning values
- * "wide_tile_log2" and "wide_fuse").
+ * workgroup).  Library choices (0): tile_log2 13 (11 from 2^12 to 2^16
+ * elements), fuse 8 (tuning values "wide_tile_log2" and "wide_fuse").
  */
 int bitonic_sort_wide_plan(void* keys, int32_t* values, int64_t n, int key_type, int ascending,
                            const bitonic_plan* plan, void* stream);

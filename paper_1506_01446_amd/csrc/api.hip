@@ -254,7 +254,12 @@ static int64_t enqueue_plain(int32_t* keys, uint32_t n, int K, Codec flip, const
     // Phases 1..K.  The scalar-access tile sorts 2^13-key tiles, which is
     // phases 1..K only when one tile holds all n keys (K == k); fewer phases
     // of a longer array run in the LDS network.
-    if (K < kTileMinLog2 || (r.scalar_io && K < kScalarTileLog2 && K < k))
+    // An array of up to 2^12 keys is one tile of at least 2^9.
+    if (K == k && K < kTileMinLog2 && !r.scalar_io && r.sort_kind == 4)
+      emit(tile_shape(BITONIC_LAUNCH_TILE_SORT, K < kFewTilesMinLog2 ? kFewTilesMinLog2 : K), [&] {
+        launch_tile(K < kFewTilesMinLog2 ? kFewTilesMinLog2 : K, 4, keys, n, flip, CX_BOTH, 0, st);
+      });
+    else if (K < kTileMinLog2 || (r.scalar_io && K < kScalarTileLog2 && K < k))
       emit(tile_shape(BITONIC_LAUNCH_LDS_NETWORK, K),
            [&] { launch_lds_network(K, 1, K, false, keys, n, flip, st); });
     else if (r.scalar_io)
@@ -472,17 +477,11 @@ static WorkspaceCache<PoolAlloc> g_workspaces;
 // grows below 2^18 elements (its launches and their fixed latencies: 40 us
 // for 4-byte keys, 65 to 75 us for 8-byte elements), the network's does with
 // every phase; measured on MI355X in us, network against digits:
-//   4-byte keys  2^16  33.7, 39.7   2^17  41.0, 40.0   2^18  51.6, 42.3
-//     ragged     2^14.5  35.4, 40.6   2^15.1  43.9, 40.6   2^16.5  53.9, 41.2
-//   8-byte keys  2^15  63.9, 63.7   2^15.1  76.4, 63.0   2^17  93.1, 68.4
-//   pairs        2^15  63.8, 69.5   2^15.1  76.3, 69.1   2^17  90.0, 74.6
-// The network is slower on a size that is not a power of two, the digit sort
-// is not.
-static bool digits_pay(int64_t n, bool wide) {
-  if (n > kRadixMaxN) return false;
-  const bool ragged = (n & (n - 1)) != 0;
-  return n > int64_t(1) << (wide || ragged ? 15 : 16);
-}
+//   4-byte keys  50000  36.5, 40.8   2^16  30.8, 39.7   10^5  51.3, 42.2
+//                2^17   38.7, 41.0   2^18  47.7, 43.8
+//   8-byte keys  50000  55.4, 63.1   2^16  54.3, 65.5   10^5  72.1, 66.0
+//                2^17   71.6, 68.9   2^18  96.2, 76.4
+static bool digits_pay(int64_t n) { return n > int64_t(1) << 16 && n <= kRadixMaxN; }
 
 // The digit sort of d's n elements, if it is the faster way and can be had:
 // false (nothing enqueued) for sizes the network sorts faster, on a stream
@@ -490,7 +489,7 @@ static bool digits_pay(int64_t n, bool wide) {
 // later calls), and where the workspace cannot be allocated.
 static bool sort_by_digits(const RadixData& d, int64_t n, hipStream_t st) {
   const bool wide = d.keys64 || d.values;
-  if (!digits_pay(n, wide)) return false;
+  if (!digits_pay(n)) return false;
   int dev = 0;
   if (stream_is_capturing(st) || current_device(&dev) != BITONIC_OK) return false;
   const size_t bytes = radix_space(nullptr, (uint32_t)n, wide ? 8 : 4, nullptr);
@@ -684,7 +683,7 @@ static int64_t enqueue_wide(int64_t* k64, int32_t* k32, int32_t* vals, uint32_t 
   };
   auto tile_shape = [&](int kind, int Lt) { return bitonic_launch_shape{kind, 0, Lt, 0, unit, 64}; };
   if (K <= L) {
-    const int Lt = K < kWideTileMinLog2 ? kWideTileMinLog2 : K;
+    const int Lt = K < kWideSmallLog2 ? kWideSmallLog2 : K;
     emit(tile_shape(BITONIC_LAUNCH_TILE_SORT, Lt),
          [&] { launch_wide_tile(Lt, 0, k64, k32, vals, n, cd, CX_BOTH, st); });
     return launches;
@@ -723,10 +722,15 @@ static int64_t enqueue_wide(int64_t* k64, int32_t* k32, int32_t* vals, uint32_t 
   return launches;
 }
 
-static int resolve_wide(const bitonic_plan* plan, int* L, int* F) {
+static int resolve_wide(const bitonic_plan* plan, int64_t n, int* L, int* F) {
   load_env_tuning_once();
   *L = g_wide_tile_log2.load();
   *F = g_wide_fuse.load();
+  // Between one tile's size and 2^16 elements the smallest tiles: a larger one
+  // keeps fewer compute units busy for longer (int64 on MI355X, 2^13- against
+  // 2^11-element tiles: 2^13 34.7 and 25.9 us, 2^14 49.2 and 33.7, 2^16 74.0
+  // and 54.3).
+  if (n > int64_t(1) << kFewTilesMaxLog2 && n <= int64_t(1) << 16) *L = kWideTileMinLog2;
   if (plan) {
     if (plan->kind != BITONIC_PLAN_AUTO && plan->kind != BITONIC_PLAN_OPTIMIZED)
       return BITONIC_EINVAL;
@@ -755,7 +759,7 @@ static int sort_wide(void* keys, int32_t* values, int64_t n, int key_type, int a
       (reinterpret_cast<uintptr_t>(values) & 3u) != 0)
     return BITONIC_EINVAL;
   int L = 0, F = 0;
-  const int rc = resolve_wide(plan, &L, &F);
+  const int rc = resolve_wide(plan, n, &L, &F);
   if (rc) return rc;
   if (n <= 1) return BITONIC_OK;
   const Codec64 cd = pairs ? make_pair_codec(key_type, ascending != 0)
@@ -878,7 +882,7 @@ int bitonic_sort_wide_plan(void* keys, int32_t* values, int64_t n, int key_type,
 int64_t bitonic_wide_plan_passes(int64_t n, const bitonic_plan* plan) {
   if (n < 0 || n > (int64_t(1) << 31)) return -1;
   int L = 0, F = 0;
-  if (resolve_wide(plan, &L, &F)) return -1;
+  if (resolve_wide(plan, n, &L, &F)) return -1;
   if (n <= 1) return 0;
   return enqueue_wide(nullptr, nullptr, nullptr, (uint32_t)n, Codec64{0, 0}, L, F, nullptr, true);
 }
@@ -930,7 +934,7 @@ int64_t bitonic_plan_shapes(int64_t n, int layout, const bitonic_plan* plan,
     case BITONIC_LAYOUT_KEYS64:
     case BITONIC_LAYOUT_PAIRS: {
       int L = 0, F = 0;
-      if (resolve_wide(plan, &L, &F)) return -1;
+      if (resolve_wide(plan, n, &L, &F)) return -1;
       if (n <= 1) return 0;
       return enqueue_wide(nullptr, nullptr, nullptr, (uint32_t)n, Codec64{0, 0}, L, F, nullptr,
                           true, &obs, layout == BITONIC_LAYOUT_KEYS64 ? 8 : 4);

@@ -122,6 +122,42 @@ __device__ __forceinline__ int32_t lane_pair_step(int32_t x, int32_t c) {
   }
 }
 
+// The same for 8-byte elements: both words moved, the element kept by one
+// 64-bit compare (`upper`: the lane holds the upper end of the pair).
+template <uint32_t M>
+__device__ __forceinline__ int64_t lane_xor64(int64_t v) {
+  const uint64_t u = (uint64_t)v;
+  const uint32_t lo = (uint32_t)lane_xor<M>((int32_t)(uint32_t)u);
+  const uint32_t hi = (uint32_t)lane_xor<M>((int32_t)(uint32_t)(u >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+__device__ __forceinline__ int64_t keep_of_pair64(int64_t a, int64_t b, bool upper) {
+  return (a < b) == upper ? b : a;
+}
+
+template <uint32_t M>
+__device__ __forceinline__ int64_t lane_pair_step64(int64_t x, bool upper) {
+  if constexpr (M == 16 || M == 32) {
+    const uint32_t lo = (uint32_t)(uint64_t)x, hi = (uint32_t)((uint64_t)x >> 32);
+    int64_t a, b;
+    if constexpr (M == 16) {
+      const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+      const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+      a = (int64_t)(((uint64_t)h[0] << 32) | l[0]);
+      b = (int64_t)(((uint64_t)h[1] << 32) | l[1]);
+    } else {
+      const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+      const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+      a = (int64_t)(((uint64_t)h[0] << 32) | l[0]);
+      b = (int64_t)(((uint64_t)h[1] << 32) | l[1]);
+    }
+    return keep_of_pair64(a, b, upper);
+  } else {
+    return keep_of_pair64(x, lane_xor64<M>(x), upper);
+  }
+}
+
 // All compare-exchange steps of group G on the registers.
 template <class PR, int G, class E>
 __device__ __forceinline__ void group_steps(E (&x)[PR::R]) {
@@ -143,10 +179,25 @@ __device__ __forceinline__ void group_steps(E (&x)[PR::R]) {
     } else {
       // lane step: every slot meets a slot of lane (lane XOR M); the lane
       // whose bit highbit(M) is set holds the upper end of all its pairs
-      static_assert(sizeof(E) == 4, "lane steps move 4-byte keys");
       constexpr uint32_t M = step_lane(D);
       constexpr uint32_t DR = step_reg(D);
       const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+      if constexpr (sizeof(E) == 8) {
+        const bool upper = ((lane >> highbit(M)) & 1u) != 0;
+        static_for<0, PR::R>([&](auto J) {
+          constexpr uint32_t j = J;
+          constexpr uint32_t jj = j ^ DR;
+          if constexpr (DR == 0) {
+            x[j] = lane_pair_step64<M>(x[j], upper);
+          } else if constexpr (j < jj) {
+            const int64_t pa = lane_xor64<M>(x[jj]);
+            const int64_t pb = lane_xor64<M>(x[j]);
+            x[j] = keep_of_pair64(x[j], pa, upper);
+            x[jj] = keep_of_pair64(x[jj], pb, upper);
+          }
+        });
+        return;
+      } else {
       const int32_t c = ((lane >> highbit(M)) & 1u) ? INT32_MAX : INT32_MIN;
       static_for<0, PR::R>([&](auto J) {
         constexpr uint32_t j = J;
@@ -160,6 +211,7 @@ __device__ __forceinline__ void group_steps(E (&x)[PR::R]) {
           x[jj] = keep_of_pair(x[jj], pb, c);
         }
       });
+      }
     }
   });
 }

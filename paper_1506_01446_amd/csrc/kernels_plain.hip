@@ -78,6 +78,7 @@ bool tile_log2_supported(int L) { return L >= kTileMinLog2 && L <= kTileMaxLog2;
 
 void launch_tile(int L, int kind, int32_t* keys, uint32_t n, Codec cd, int cx,
                  uint32_t max_blocks, hipStream_t st) {
+  if (few_tiles(n, L) && launch_tile_few(L, kind, keys, n, cd, cx, st)) return;
   switch (L) {
     case 11: launch_tile_L<11>(kind, keys, n, cd, cx, max_blocks, st); break;
     case 12: launch_tile_L<12>(kind, keys, n, cd, cx, max_blocks, st); break;

@@ -14,9 +14,10 @@
 // elements (8-byte accesses for int64 keys, a 4-byte access into each array
 // for pairs), which needs no alignment beyond the element's own.
 //
-//  wide_tile_kernel<L, KIND, CX, ST>  tile sort (KIND 2), merge (KIND 3) or
-//                                     phase L (KIND 7: phase t+1 on tiles
-//                                     twice the sort's tile)
+//  wide_tile_kernel<L, RL, KIND, CX, ST>  tile sort (KIND 6), merge (KIND 3)
+//                                     or phase L (KIND 7: phase t+1 on tiles
+//                                     twice the sort's tile), 2^RL elements
+//                                     per thread
 //  column_pass_kernel<F, MIRROR, B, ST>  F long-stride steps, one column of
 //                                        2^F elements per thread (column_pass.hpp)
 //  wide_lanes_pass_kernel<FR, G, MIRROR, ST>  F = FR + G = 7, 8 steps, each
@@ -32,13 +33,17 @@
 
 namespace bitonic {
 
-// One tile of 2^L elements per workgroup, `valid` of them real.
-template <int L, int KIND, int CX, class ST>
-__global__ __launch_bounds__(1 << (L - kWideRegLog)) void wide_tile_kernel(ST st, uint32_t n,
-                                                                           Codec64 codec) {
-  using PR = Prog<L, kWideRegLog, KIND>;
+// One tile of 2^L elements per workgroup, `valid` of them real.  16 elements
+// per thread (RL = 4) regroup through 4-byte LDS words; with fewer, the
+// programs of launches with few tiles, whose workgroups need not share a CU,
+// through 8-byte words.
+template <int L, int RL, int KIND, int CX, class ST>
+__global__ __launch_bounds__(1 << (L - RL)) void wide_tile_kernel(ST st, uint32_t n,
+                                                                  Codec64 codec) {
+  using PR = Prog<L, RL, KIND>;
   constexpr int LAST = PR::value.ngroups - 1;
-  __shared__ uint32_t lds[PR::LDSW];  // 4-byte words: run_from_split
+  constexpr bool SPLIT = RL == kWideRegLog;
+  __shared__ __attribute__((aligned(8))) uint32_t lds[PR::LDSW * (SPLIT ? 1 : 2)];
   const KeyIO<CX, Codec64> cd{codec};
   const uint32_t t0 = (uint32_t)blockIdx.x << L;
   const uint32_t left = n - t0;
@@ -58,7 +63,10 @@ __global__ __launch_bounds__(1 << (L - kWideRegLog)) void wide_tile_kernel(ST st
       });
     }
   }
-  run_from_split<PR, 0>(x, lds, threadIdx.x);
+  if constexpr (SPLIT)
+    run_from_split<PR, 0>(x, lds, threadIdx.x);
+  else
+    run_from<PR, 0>(x, reinterpret_cast<int64_t*>(lds), threadIdx.x);
   {
     uint32_t tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
@@ -73,20 +81,6 @@ __global__ __launch_bounds__(1 << (L - kWideRegLog)) void wide_tile_kernel(ST st
       });
     }
   }
-}
-
-// An 8-byte element's value in lane (this lane XOR M): both words moved.
-template <uint32_t M>
-__device__ __forceinline__ int64_t lane_xor64(int64_t v) {
-  const uint64_t u = (uint64_t)v;
-  const uint32_t lo = (uint32_t)lane_xor<M>((int32_t)(uint32_t)u);
-  const uint32_t hi = (uint32_t)lane_xor<M>((int32_t)(uint32_t)(u >> 32));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// The element a lane keeps from the pair (a, b): the larger where `upper`.
-__device__ __forceinline__ int64_t keep_of_pair64(int64_t a, int64_t b, bool upper) {
-  return (a < b) == upper ? b : a;
 }
 
 // F = FR + G long-stride steps of an 8-byte sort with every column of a
@@ -148,53 +142,70 @@ __global__ __launch_bounds__(256) void wide_lanes_pass_kernel(ST st, int q) {
 // ---------------------------------------------------------------------------
 // launchers
 
-template <int L, class ST>
-static void launch_wide_tile_L(int kind, ST st, uint32_t n, Codec64 cd, int cx, hipStream_t s) {
-  const uint32_t ntiles = (uint32_t)(((uint64_t)n + (1u << L) - 1) >> L);
-  constexpr int NT = 1 << (L - kWideRegLog);
-  if (codec_is_identity(cd)) cx = CX_NONE;
-  if (kind == 0) {
-    if (cx == CX_NONE)
-      wide_tile_kernel<L, 2, CX_NONE, ST><<<ntiles, NT, 0, s>>>(st, n, cd);
-    else if (cx == CX_ENC)
-      wide_tile_kernel<L, 2, CX_ENC, ST><<<ntiles, NT, 0, s>>>(st, n, cd);
-    else
-      wide_tile_kernel<L, 2, CX_BOTH, ST><<<ntiles, NT, 0, s>>>(st, n, cd);
-  } else if (cx == CX_NONE) {
-    wide_tile_kernel<L, 3, CX_NONE, ST><<<ntiles, NT, 0, s>>>(st, n, cd);
-  } else {
-    wide_tile_kernel<L, 3, CX_DEC, ST><<<ntiles, NT, 0, s>>>(st, n, cd);
-  }
+template <int L, int RL, int KIND, int CX, class ST>
+static void launch_wide(ST st, uint32_t n, Codec64 cd, hipStream_t s) {
+  wide_tile_kernel<L, RL, KIND, CX, ST><<<((n - 1) >> L) + 1, 1 << (L - RL), 0, s>>>(st, n, cd);
 }
 
+// A tile sort (kind 6: with lane steps) or a merge or phase.
+template <int L, int RL, class ST>
+static void launch_wide_sort(ST st, uint32_t n, Codec64 cd, int cx, hipStream_t s) {
+  if (cx == CX_NONE) launch_wide<L, RL, 6, CX_NONE>(st, n, cd, s);
+  else if (cx == CX_ENC) launch_wide<L, RL, 6, CX_ENC>(st, n, cd, s);
+  else launch_wide<L, RL, 6, CX_BOTH>(st, n, cd, s);
+}
+template <int L, int RL, int KIND, class ST>
+static void launch_wide_merge(ST st, uint32_t n, Codec64 cd, int cx, hipStream_t s) {
+  if (cx == CX_NONE) launch_wide<L, RL, KIND, CX_NONE>(st, n, cd, s);
+  else launch_wide<L, RL, KIND, CX_DEC>(st, n, cd, s);
+}
+
+// Launches of few tiles (few_tiles) take 8 elements per thread (4 for 2^10):
+// one tile sort on MI355X, 16 against 8 per thread, 2^11 elements 15.1 and
+// 10.0 us, 2^12 20.8 and 16.4, and 2^10 with 4 per thread 5.7; on a full chip
+// (2^23 elements) 2^12-element tiles take 72 us with either.
 template <class ST>
 static void launch_wide_tile_st(int L, int kind, ST st, uint32_t n, Codec64 cd, int cx,
                                 hipStream_t s) {
-  switch (L) {
-    case 11: launch_wide_tile_L<11>(kind, st, n, cd, cx, s); break;
-    case 12: launch_wide_tile_L<12>(kind, st, n, cd, cx, s); break;
-    case 13: launch_wide_tile_L<13>(kind, st, n, cd, cx, s); break;
-    default: break;
-  }
-}
-
-template <int L, class ST>
-static void launch_wide_phase_L(ST st, uint32_t n, Codec64 cd, int cx, hipStream_t s) {
-  const uint32_t ntiles = (uint32_t)(((uint64_t)n + (1u << L) - 1) >> L);
-  constexpr int NT = 1 << (L - kWideRegLog);
   if (codec_is_identity(cd)) cx = CX_NONE;
-  if (cx == CX_NONE)
-    wide_tile_kernel<L, 7, CX_NONE, ST><<<ntiles, NT, 0, s>>>(st, n, cd);
-  else
-    wide_tile_kernel<L, 7, CX_DEC, ST><<<ntiles, NT, 0, s>>>(st, n, cd);
+  const bool few = few_tiles(n, L);
+  if (kind == 0) {
+    switch (L) {
+      case 10: launch_wide_sort<10, 2>(st, n, cd, cx, s); break;
+      case 11:
+        if (few) launch_wide_sort<11, 3>(st, n, cd, cx, s);
+        else launch_wide_sort<11, kWideRegLog>(st, n, cd, cx, s);
+        break;
+      case 12:
+        if (few) launch_wide_sort<12, 3>(st, n, cd, cx, s);
+        else launch_wide_sort<12, kWideRegLog>(st, n, cd, cx, s);
+        break;
+      case 13: launch_wide_sort<13, kWideRegLog>(st, n, cd, cx, s); break;
+      default: break;
+    }
+  } else {
+    switch (L) {
+      case 11:
+        if (few) launch_wide_merge<11, 3, 3>(st, n, cd, cx, s);
+        else launch_wide_merge<11, kWideRegLog, 3>(st, n, cd, cx, s);
+        break;
+      case 12: launch_wide_merge<12, kWideRegLog, 3>(st, n, cd, cx, s); break;
+      case 13: launch_wide_merge<13, kWideRegLog, 3>(st, n, cd, cx, s); break;
+      default: break;
+    }
+  }
 }
 
 template <class ST>
 static void launch_wide_phase_st(int L, ST st, uint32_t n, Codec64 cd, int cx, hipStream_t s) {
+  if (codec_is_identity(cd)) cx = CX_NONE;
   switch (L) {
-    case 12: launch_wide_phase_L<12>(st, n, cd, cx, s); break;
-    case 13: launch_wide_phase_L<13>(st, n, cd, cx, s); break;
-    case 14: launch_wide_phase_L<14>(st, n, cd, cx, s); break;
+    case 12:
+      if (few_tiles(n, L)) launch_wide_merge<12, 3, 7>(st, n, cd, cx, s);
+      else launch_wide_merge<12, kWideRegLog, 7>(st, n, cd, cx, s);
+      break;
+    case 13: launch_wide_merge<13, kWideRegLog, 7>(st, n, cd, cx, s); break;
+    case 14: launch_wide_merge<14, kWideRegLog, 7>(st, n, cd, cx, s); break;
     default: break;
   }
 }

@@ -29,6 +29,23 @@ bool tile_log2_supported(int L);
 void launch_tile(int L, int kind, int32_t* keys, uint32_t n, Codec cd, int cx,
                  uint32_t max_blocks, hipStream_t st);
 
+// The same programs with eight keys per thread, for launches of few tiles
+// (few_tiles): tile sort of kind 4 (L = 9 .. 12), merge (L = 12), phase
+// (L = 13), one tile per workgroup.  False (nothing launched) for another
+// kind or L.
+bool launch_tile_few(int L, int kind, int32_t* keys, uint32_t n, Codec cd, int cx, hipStream_t st);
+
+// With at most 64 tiles on 256 compute units a launch takes as long as one
+// tile does, and that is the shorter the more threads share its steps, even
+// where they then meet through lane steps and LDS more often.  One tile sort
+// on MI355X, 32 against 8 keys per thread: 2^11 keys 7.0 and 4.1 us, 2^12
+// 9.2 and 6.1 (2^10 3.5, 2^9 2.7); on a full chip (2^24 keys) 2^12-key tiles
+// take 52 and 57 us.
+constexpr uint32_t kFewTiles = 64;
+constexpr int kFewTilesMinLog2 = 9;
+constexpr int kFewTilesMaxLog2 = 12;
+constexpr bool few_tiles(uint32_t n, int L) { return (n - 1) >> L < kFewTiles; }
+
 // Arrays that do not start on a 16-byte boundary: tile sort (kind 0) or merge
 // (kind 1) of 2^kScalarTileLog2-key tiles whose global accesses put lanes on
 // consecutive keys (4-byte alignment suffices).  cx as for launch_tile.
@@ -73,6 +90,7 @@ void launch_step(int sb, bool mirror, int32_t* keys, uint32_t n, uint32_t N, Cod
 // elements, up to kWideFuseMax steps per pass.
 constexpr int kWideRegLog = 4;
 constexpr int kWideTileMinLog2 = 11;
+constexpr int kWideSmallLog2 = 10;  // the tile of a sort of up to 2^10 elements
 constexpr int kWideTileMaxLog2 = 13;
 constexpr int kWideFuseMaxColumn = 6;  // steps one thread's registers hold
 constexpr int kWideFuseMax = 8;        // with a column split over lanes (lane passes)
