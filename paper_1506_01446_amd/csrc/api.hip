@@ -568,10 +568,11 @@ static int64_t enqueue_segmented(const SegData& d, const int64_t* offsets, int64
     launch_seg_prep(offsets, nseg, sc, T, validated, radix_cls,
                     digits ? &digits->meta->trivial[0] : nullptr, st);
   });
+  const bool few = seg_small_few(nseg, ceil_log2(max_seg_len), T == kSegTileLog64);
   const int64_t slots = (int64_t)cus * g_seg_bpc.load();
   const int small_grid = (int)(slots < nseg ? slots : nseg);
   emit({BITONIC_LAUNCH_SEG_SMALL, 0, kSegSmallMaxLog2, 0, unit, 64},
-       [&] { launch_seg_small(d, offsets, sc, small_grid, st); });
+       [&] { launch_seg_small(d, offsets, sc, small_grid, few, st); });
   int M = ceil_log2(max_seg_len);
   if (M <= kSegSmallMaxLog2) return launches;
   if (digits) {

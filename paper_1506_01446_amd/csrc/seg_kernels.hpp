@@ -77,28 +77,42 @@ __device__ __forceinline__ void seg_tile_program(ST tile, uint32_t valid, CD cd,
   }
 }
 
-// The scalar-I/O tile-sort program of a storage: with lane steps (kind 6)
-// for 4-byte keys, without (kind 2) for 8-byte elements.
-template <class ST>
-constexpr int seg_sort_kind() {
-  return sizeof(typename ST::E) == 4 ? 6 : 2;
-}
+// The scalar-I/O tile-sort program, with lane steps.
+constexpr int kSegSortKind = 6;
 
 // ---------------------------------------------------------------------------
 // small segments
 
-constexpr uint32_t kSmallLdsWords = (kSegThreads << kTileRegLogSeg) / 32 * 33;
+// Elements per thread, log2: 8 where there are few segments (seg_small_few),
+// so that the longest one's workgroup has 16 waves; else 32 4-byte keys or 16
+// 8-byte elements, which take fewer lane steps and regroups.
+constexpr int kSegFewRegLog = 3;
+template <class ST>
+constexpr int seg_many_reg_log() {
+  return sizeof(typename ST::E) == 8 ? 4 : kTileRegLogSeg;
+}
+
+// Threads of a small-segment workgroup: one segment of the largest class.
+constexpr int seg_small_threads(int RL) { return 1 << (kSegSmallMaxLog2 - RL); }
+
+// Whether the elements regroup through 4-byte LDS words: the 8-byte ones of
+// the kernel for many segments, so that four workgroups share a CU.
+template <class ST, int RL>
+constexpr bool seg_small_split() {
+  return sizeof(typename ST::E) == 8 && RL == seg_many_reg_log<ST>();
+}
 
 // Not inlined: each class's program keeps its own register allocation
 // instead of the kernel carrying the union of all of them.
-template <int L, class ST, class CD>
+template <int L, int RL, class ST, class CD>
 __device__ __attribute__((noinline)) void seg_small_item(ST keys,
                                                const int64_t* __restrict__ offsets,
                                                const uint32_t* __restrict__ ids, uint32_t first,
-                                               uint32_t count, CD cd, typename ST::E* lds) {
-  using PR = Prog<L, kTileRegLogSeg, seg_sort_kind<ST>()>;
+                                               uint32_t count, CD cd, uint32_t* lds) {
+  using PR = Prog<L, RL, kSegSortKind>;
   constexpr uint32_t NT = PR::NT;
-  static_assert((kSegThreads / NT) * PR::LDSW <= kSmallLdsWords, "padded tiles exceed LDS");
+  constexpr bool SPLIT = seg_small_split<ST, RL>();
+  constexpr uint32_t WORDS = PR::LDSW * (SPLIT ? 1 : sizeof(typename ST::E) / 4);
   const uint32_t grp = threadIdx.x / NT;
   const uint32_t ltid = threadIdx.x % NT;
   ST p = keys;
@@ -109,15 +123,18 @@ __device__ __attribute__((noinline)) void seg_small_item(ST keys,
     p = keys.at(off);
     len = (uint32_t)(offsets[s + 1] - off);
   }
-  seg_tile_program<PR>(p, len, cd, lds + grp * PR::LDSW, ltid);
+  seg_tile_program<PR, SPLIT>(p, len, cd, reinterpret_cast<typename ST::E*>(lds + grp * WORDS),
+                              ltid);
 }
 
-template <class ST, class CD>
-__global__ __launch_bounds__(kSegThreads) void seg_small_kernel(
+template <int RL, class ST, class CD>
+__global__ __launch_bounds__(seg_small_threads(RL)) void seg_small_kernel(
     ST keys, const int64_t* __restrict__ offsets, SegMeta* __restrict__ meta,
     const uint32_t* __restrict__ small_ids, CD cd) {
-  // room for 256 / 2^(m-5) padded tiles of 2^m elements, for every class m
-  __shared__ typename ST::E lds[kSmallLdsWords];
+  // room for the 2^(13 - m) padded tiles of an item of class m, for every m
+  __shared__ __attribute__((aligned(8)))
+  uint32_t lds[(seg_small_threads(RL) * ((1 << RL) + 1)) *
+               (seg_small_split<ST, RL>() ? 1 : sizeof(typename ST::E) / 4)];
   __shared__ uint32_t item_s;
   const uint32_t total = meta->small_items;
   for (;;) {
@@ -135,15 +152,15 @@ __global__ __launch_bounds__(kSegThreads) void seg_small_kernel(
     const uint32_t left = meta->small_count[ci] - k * per;
     const uint32_t count = left < per ? left : per;
     switch (cls) {
-      case 13: seg_small_item<13>(keys, offsets, small_ids, first, count, cd, lds); break;
-      case 12: seg_small_item<12>(keys, offsets, small_ids, first, count, cd, lds); break;
-      case 11: seg_small_item<11>(keys, offsets, small_ids, first, count, cd, lds); break;
-      case 10: seg_small_item<10>(keys, offsets, small_ids, first, count, cd, lds); break;
-      case 9: seg_small_item<9>(keys, offsets, small_ids, first, count, cd, lds); break;
-      case 8: seg_small_item<8>(keys, offsets, small_ids, first, count, cd, lds); break;
-      case 7: seg_small_item<7>(keys, offsets, small_ids, first, count, cd, lds); break;
-      case 6: seg_small_item<6>(keys, offsets, small_ids, first, count, cd, lds); break;
-      default: seg_small_item<5>(keys, offsets, small_ids, first, count, cd, lds); break;
+      case 13: seg_small_item<13, RL>(keys, offsets, small_ids, first, count, cd, lds); break;
+      case 12: seg_small_item<12, RL>(keys, offsets, small_ids, first, count, cd, lds); break;
+      case 11: seg_small_item<11, RL>(keys, offsets, small_ids, first, count, cd, lds); break;
+      case 10: seg_small_item<10, RL>(keys, offsets, small_ids, first, count, cd, lds); break;
+      case 9: seg_small_item<9, RL>(keys, offsets, small_ids, first, count, cd, lds); break;
+      case 8: seg_small_item<8, RL>(keys, offsets, small_ids, first, count, cd, lds); break;
+      case 7: seg_small_item<7, RL>(keys, offsets, small_ids, first, count, cd, lds); break;
+      case 6: seg_small_item<6, RL>(keys, offsets, small_ids, first, count, cd, lds); break;
+      default: seg_small_item<5, RL>(keys, offsets, small_ids, first, count, cd, lds); break;
     }
   }
 }
@@ -474,10 +491,17 @@ void seg_run(ST keys, CD cd, const SegLaunch& l, const int64_t* offsets, const S
              hipStream_t st) {
   switch (l.what) {
     case SegLaunch::kSmall:
-      seg_small_kernel<<<l.grid, kSegThreads, 0, st>>>(keys, offsets, sc.meta, sc.small_ids, cd);
+      if (l.few)
+        seg_small_kernel<kSegFewRegLog>
+            <<<l.grid, seg_small_threads(kSegFewRegLog), 0, st>>>(keys, offsets, sc.meta,
+                                                                  sc.small_ids, cd);
+      else
+        seg_small_kernel<seg_many_reg_log<ST>()>
+            <<<l.grid, seg_small_threads(seg_many_reg_log<ST>()), 0, st>>>(
+                keys, offsets, sc.meta, sc.small_ids, cd);
       break;
     case SegLaunch::kTileSort:
-      seg_tile_kernel<seg_sort_kind<ST>()><<<l.grid, seg_tile_threads<ST>(), 0, st>>>(
+      seg_tile_kernel<kSegSortKind><<<l.grid, seg_tile_threads<ST>(), 0, st>>>(
           keys, offsets, sc.meta, sc.big_ids, sc.big_tiles, l.cls, cd);
       break;
     case SegLaunch::kTileMerge:

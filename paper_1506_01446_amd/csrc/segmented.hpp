@@ -93,6 +93,23 @@ struct SegData {
   Codec64 cd64;
 };
 
+// Whether the small segments take the kernel for few of them (eight elements
+// per thread).  It is the faster one while the chip is not full of workgroups
+// of the other; 4-byte segments of up to 2^6 keys are a thread's or two's
+// registers there.  Measured on MI355X in us with the copy that restores the
+// input, kernel for many against few (and before it, 8-byte elements at 32
+// per thread):
+//   lengths to       2^5          2^8          2^11         2^13
+//   4-byte     64    16.7, 16.9   21.7, 18.0   28.1, 21.6   31.5, 27.4
+//             256    17.8, 18.4   24.1, 21.2   31.0, 24.6   34.9, 31.7
+//            8192    43.3, 43.3   46.1, 43.8   67.9, 84.3   298, 299
+//   8-byte     64    19.4, 18.0   27.4, 23.6   37.0, 33.0   47.2, 47.3 (86.4)
+//            2048    36.4, 34.5   49.4, 39.4   72.0, 68.6   125, 161  (204)
+constexpr bool seg_small_few(int64_t nseg, int max_log2, bool wide) {
+  const int top = max_log2 < kSegSmallMaxLog2 ? max_log2 : kSegSmallMaxLog2;
+  return (wide || top > 6) && nseg < (int64_t(1) << (22 - top));
+}
+
 // One launch of the sequence: the small-segment kernel, a big-segment tile
 // sort or merge of the segments of class >= cls, or a pass of f steps on
 // bits q+f-1 .. q of them.
@@ -104,6 +121,7 @@ struct SegLaunch {
   int cls;
   int q;
   int grid;
+  bool few;  // small segments: the kernel for few of them
 };
 
 // Per storage type (kernels_seg32.hip, kernels_segpairs.hip, kernels_seg64.hip).
@@ -135,7 +153,7 @@ void launch_seg_validate(const int64_t* offsets, int64_t nseg, int64_t bound, co
 // until the device is idle.  0 on success, -1 on a HIP error.
 int seg_validation_error(int32_t* code);
 void launch_seg_small(const SegData& d, const int64_t* offsets, const SegScratch& sc, int grid,
-                      hipStream_t st);
+                      bool few, hipStream_t st);
 // Tile sort (merge == false) or tile merge of the big segments of class >= cls_min.
 void launch_seg_tiles(bool merge, const SegData& d, const int64_t* offsets, const SegScratch& sc,
                       int cls_min, int grid, hipStream_t st);
