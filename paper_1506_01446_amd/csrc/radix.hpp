@@ -76,9 +76,15 @@ constexpr uint32_t radix_tiles(uint32_t n, int elem_bytes) {
   const uint32_t tile = (uint32_t)(radix_items(n, elem_bytes) * kRadixThreads);
   return n / tile + (n % tile != 0);
 }
+// Counting workgroups, of 1024 threads: one per compute unit, as the scan
+// reads a row of counts of each (whole sorts, with 512 of 512 threads before:
+// 2^22 int32 97.7 -> 93.4 us, 2^24 int64 626 -> 614, 2^24 argsort 380 -> 370);
+// two per compute unit from 2^25 elements on, where the count itself is long
+// (2^26 argsort 1417 -> 1347 us, with one 1412).
 constexpr uint32_t radix_hist_blocks(uint32_t n) {
   const uint32_t b = n / 4096 + (n % 4096 != 0);
-  return b < kRadixHistBlocks ? b : kRadixHistBlocks;
+  const uint32_t most = n >= (1u << 25) ? kRadixHistBlocks : kRadixHistBlocks / 2;
+  return b < most ? b : most;
 }
 
 // Workspace bytes of a sort of n elements of `elem_bytes` (4; 8-byte keys

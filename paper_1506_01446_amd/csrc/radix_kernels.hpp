@@ -48,7 +48,9 @@ constexpr int radix_passes() {
 // ---------------------------------------------------------------------------
 // counting
 
-constexpr int kRadixHistThreads = 512;
+// One workgroup's waves fill a CU's LDS-atomic pipe, so a share of the array
+// can be large and its rows of counts few (radix_hist_blocks).
+constexpr int kRadixHistThreads = 1024;
 
 // LDS of a counting workgroup.  A bin is kept in 64 / passes copies (64 KiB
 // in all, two workgroups per CU), lane l adding to copy l mod copies: an
@@ -63,15 +65,14 @@ struct RadixBinsLds {
 };
 
 // Counts every digit of elements lo .. hi of a (n in all) with the whole
-// workgroup; then bin b's count (pass b / 256, digit b mod 256) is
+// workgroup of NT threads; then bin b's count (pass b / 256, digit b mod 256) is
 // radix_bin_count(lds, b), and lds.decrease is 1 if a pair's value (Pairs) is
 // above the next one's.
-template <class MAP, class ST>
+template <uint32_t NT, class MAP, class ST>
 __device__ __forceinline__ void radix_count(RadixBinsLds<ST>& lds, const MAP& map, const ST& a,
                                             uint64_t lo, uint64_t hi, uint64_t n) {
   using E = typename ST::E;
   using L = RadixBinsLds<ST>;
-  constexpr uint32_t NT = kRadixHistThreads;
   const uint32_t tid = threadIdx.x;
   for (uint32_t i = tid; i < L::P * kRadixBins * L::C; i += NT) lds.bins[i] = 0;
   if (tid == 0) lds.decrease = 0;
@@ -125,7 +126,7 @@ __global__ __launch_bounds__(kRadixHistThreads) void radix_hist_kernel(
   const uint32_t per = ((n - 1) / gridDim.x / NT + 1) * NT;
   const uint64_t lo = (uint64_t)blockIdx.x * per;
   const uint64_t hi = lo + per < n ? lo + per : n;
-  radix_count(lds, RadixMap<ST, FL, CD>{cd}, a, lo, hi, n);
+  radix_count<NT>(lds, RadixMap<ST, FL, CD>{cd}, a, lo, hi, n);
   for (uint32_t b = tid; b < P * kRadixBins; b += NT)
     partial[(size_t)blockIdx.x * (P * kRadixBins) + b] = radix_bin_count(lds, b);
   if (tid == 0) unordered[blockIdx.x] = lds.decrease;

@@ -53,9 +53,15 @@ __device__ void segradix_in_place(const ST& a, uint32_t len, const MAP& map) {
     }
 }
 
+// Threads of a counting workgroup: smaller ones than a single array's, as a
+// workgroup counts one segment of its range after another, with a barrier
+// around each (a batch of 12 requests of 2^8 .. 2^22 keys: 219 us, with 1024
+// threads 221).
+constexpr int kSegRadixHistThreads = 512;
+
 // One row of a segment's counts as the passes take it: where each digit
 // begins in the segment, and whether the pass is to be left out.  All
-// kRadixHistThreads threads call it, `count` for the first 256.
+// kSegRadixHistThreads threads call it, `count` for the first 256.
 __device__ __forceinline__ void segradix_finish(uint32_t count, uint32_t len, bool ordered_values,
                                                 uint32_t* base, uint32_t* trivial,
                                                 uint32_t* wave_sum, uint32_t* one_digit) {
@@ -76,12 +82,12 @@ __device__ __forceinline__ void segradix_finish(uint32_t count, uint32_t len, bo
 // those of the segment its range begins within, in row 1 those of the one
 // that begins in it and goes on (span).
 template <bool FL, class ST, class CD>
-__global__ __launch_bounds__(kRadixHistThreads) void segradix_hist_kernel(
+__global__ __launch_bounds__(kSegRadixHistThreads) void segradix_hist_kernel(
     ST a, CD cd, const int64_t* __restrict__ offsets, const SegMeta* __restrict__ seg_meta,
     const uint32_t* __restrict__ big_ids, const uint64_t* __restrict__ big_tiles,
     SegRadixSpace s) {
   constexpr int P = radix_passes<ST>();
-  constexpr uint32_t NT = kRadixHistThreads;
+  constexpr uint32_t NT = kSegRadixHistThreads;
   constexpr uint32_t T = 1u << seg_tile_log<ST>();
   __shared__ RadixBinsLds<ST> lds;
   __shared__ uint32_t wave_sum[kRadixBins / 64];
@@ -109,7 +115,7 @@ __global__ __launch_bounds__(kRadixHistThreads) void segradix_hist_kernel(
     const uint64_t hi = (stop - first) * T < len ? (stop - first) * T : len;
     for (uint64_t t = u + tid; t < stop; t += NT)
       s.tiles[t] = SegRadixTile{off, len, i, (uint32_t)first, (uint32_t)(t - first)};
-    radix_count(lds, map, a.at(off), lo, hi, len);
+    radix_count<NT>(lds, map, a.at(off), lo, hi, len);
     if (first >= u0 && end <= uend) {
       const bool ordered = std::is_same_v<ST, Pairs> && lds.decrease == 0;
       if (tid == 0 && lds.decrease) s.meta->trivial[0] = 1;
@@ -136,12 +142,12 @@ __global__ __launch_bounds__(kRadixHistThreads) void segradix_hist_kernel(
 // Pass blockIdx.y of the segment that begins in counting range blockIdx.x and
 // goes on past it: the sum of its ranges' counts.
 template <class ST>
-__global__ __launch_bounds__(kRadixHistThreads) void segradix_scan_kernel(
+__global__ __launch_bounds__(kSegRadixHistThreads) void segradix_scan_kernel(
     const int64_t* __restrict__ offsets, const SegMeta* __restrict__ seg_meta,
     const uint32_t* __restrict__ big_ids, const uint64_t* __restrict__ big_tiles,
     SegRadixSpace s) {
   constexpr int P = radix_passes<ST>();
-  constexpr uint32_t G = kRadixHistThreads / kRadixBins;
+  constexpr uint32_t G = kSegRadixHistThreads / kRadixBins;
   constexpr uint32_t K = 32;  // loads in flight
   __shared__ uint32_t sums[G][kRadixBins];
   __shared__ uint32_t wave_sum[kRadixBins / 64];
@@ -174,7 +180,7 @@ __global__ __launch_bounds__(kRadixHistThreads) void segradix_scan_kernel(
   const bool value_pass = std::is_same_v<ST, Pairs> && pass < P / 2;
   if (value_pass && tid < rows && s.unordered[row(tid)]) down = 1;
   __syncthreads();
-  static_assert(kRadixHistBlocks <= kRadixHistThreads, "one thread per counting range");
+  static_assert(kRadixHistBlocks <= kSegRadixHistThreads, "one thread per counting range");
   c = 0;
   if (g == 0) static_for<0, (int)G>([&](auto k) { c += sums[k][d]; });
   segradix_finish(c, len, value_pass && down == 0, s.base + ((size_t)i * P + pass) * kRadixBins,
@@ -232,9 +238,9 @@ template <bool FL, class ST, class CD>
 static void segradix_launch(ST a, ST b, CD cd, const int64_t* offsets, const SegScratch& sc,
                             const SegRadixSpace& s, int cus, hipStream_t st) {
   constexpr int P = radix_passes<ST>();
-  segradix_hist_kernel<FL><<<kRadixHistBlocks, kRadixHistThreads, 0, st>>>(
+  segradix_hist_kernel<FL><<<kRadixHistBlocks, kSegRadixHistThreads, 0, st>>>(
       a, cd, offsets, sc.meta, sc.big_ids, sc.big_tiles, s);
-  segradix_scan_kernel<ST><<<dim3(kRadixHistBlocks, P), kRadixHistThreads, 0, st>>>(
+  segradix_scan_kernel<ST><<<dim3(kRadixHistBlocks, P), kSegRadixHistThreads, 0, st>>>(
       offsets, sc.meta, sc.big_ids, sc.big_tiles, s);
   // two workgroups per CU (68 KiB of LDS, 1,024 threads)
   const uint32_t grid = s.max_tiles < 2u * (uint32_t)cus ? s.max_tiles : 2u * (uint32_t)cus;
