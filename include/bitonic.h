@@ -17,12 +17,14 @@
  *    tensors); the caller owns them.  Sorting is in place.
  *  - The plain single-array sorts (bitonic_sort_i32, bitonic_sort_keys,
  *    bitonic_sort_keys64, bitonic_sort_pairs) run the network on short arrays
- *    and sort longer ones (more than 2^16 elements) by their digits, least
- *    significant first, through a workspace of the array's own
- *    size.  The result is the same (it is unique).  They run the network at
- *    every size where the workspace cannot be allocated, on a stream that is
- *    being captured into a graph, and for n = 2^31.  The calls that take a
- *    plan always run the network.
+ *    (up to 2^12 4-byte keys or 2^11 8-byte elements).  Through a workspace of
+ *    the array's own size they sort longer ones of up to 2^17 keys or 2^16
+ *    pairs by rank (the network sorts tiles, and every element goes to its
+ *    place among all of them), and the longest by their digits, least
+ *    significant first.  The result is the same (it is unique).  They run the
+ *    network at every size where the workspace cannot be allocated, on a
+ *    stream that is being captured into a graph, and for n = 2^31.  The calls
+ *    that take a plan always run the network.
  *  - `stream` is a hipStream_t (NULL = the legacy default stream).  Calls are
  *    asynchronous: they enqueue kernels on `stream` and return; the keys are
  *    sorted once the stream reaches that point.  The host never blocks.
@@ -48,8 +50,8 @@
  *    since work enqueued earlier may still use it, so no call waits for the
  *    stream.  Segmented calls on one stream are ordered by the stream, calls
  *    on different streams use different buffers.
- *  - The workspace of a digit sort (the array's size plus about 2 %, and 2
- *    to 4 MiB) comes from a memory pool of the library.  A buffer of up to
+ *  - The workspace of a sort by rank (the array's size) or by digits (plus
+ *    about 2 %, and 2 to 4 MiB) comes from a memory pool of the library.  A buffer of up to
  *    256 MiB is kept per (device, stream), at most 32 of them and 2 GiB in
  *    all, and given back for a smaller one when 64 calls in a row have needed
  *    an eighth of it or less; any other workspace is allocated for the call
@@ -78,8 +80,8 @@ enum bitonic_status {
 const char* bitonic_status_string(int status);
 
 /*
- * Sort keys[0, n) in place (sections 3.1-3.3, 4.1, 4.2; long arrays by
- * digits, see above).
+ * Sort keys[0, n) in place (sections 3.1-3.3, 4.1, 4.2; longer arrays by
+ * rank or digits, see above).
  *   keys       device pointer to n int32 keys (may be NULL when n <= 1)
  *   n          number of keys, 0 <= n <= 2^31; n <= 1 enqueues nothing
  *   ascending  nonzero: ascending; zero: descending
@@ -119,8 +121,8 @@ int bitonic_sort_keys(void* keys, int64_t n, int key_type, int ascending, void* 
 
 /*
  * Sort n 8-byte keys in place: the network of sections 3.1-3.3 with the
- * tile sort and fused passes of sections 4.1-4.2 on 8-byte elements (long
- * arrays by digits, see above).
+ * tile sort and fused passes of sections 4.1-4.2 on 8-byte elements (longer
+ * arrays by rank or digits, see above).
  *   keys       device pointer to n keys of key_type (BITONIC_KEY_I64, U64
  *              or F64), 8-byte aligned (may be NULL when n <= 1)
  *   n, ascending, stream  as for bitonic_sort_i32

@@ -2,8 +2,10 @@
 // keys, of 8-byte keys and of (key, value) pairs, the segmented sort, graph
 // capture, tuning.
 //
-// The plain sorts of long arrays go by digits (radix.hpp, sort_by_digits);
-// shorter ones, explicit plans and captured streams run the network.
+// The plain sorts go through a workspace where that is faster
+// (sort_through_workspace): middle sizes by rank (rank.hpp), long arrays by
+// digits (radix.hpp); the shortest, explicit plans and captured streams run
+// the network.
 //
 // The planner maps the k(k+1)/2 steps of the network for N = 2^k keys
 // (sections 3.2, 3.3) onto kernel launches, all enqueued on the caller's
@@ -29,6 +31,7 @@
 #include "bitonic.h"
 #include "launch.hpp"
 #include "radix.hpp"
+#include "rank.hpp"
 #include "scratch_cache.hpp"
 #include "segmented.hpp"
 #include "segradix.hpp"
@@ -473,29 +476,26 @@ struct PoolAlloc {
 };
 static WorkspaceCache<PoolAlloc> g_workspaces;
 
-// Whether the digit sort is the faster way for n elements.  Its cost hardly
-// grows below 2^18 elements (its launches and their fixed latencies: 40 us
-// for 4-byte keys, 65 to 75 us for 8-byte elements), the network's does with
-// every phase; measured on MI355X in us, network against digits:
-//   4-byte keys  50000  36.5, 40.8   2^16  30.8, 39.7   10^5  51.3, 42.2
-//                2^17   38.7, 41.0   2^18  47.7, 43.8
-//   8-byte keys  50000  55.4, 63.1   2^16  54.3, 65.5   10^5  72.1, 66.0
-//                2^17   71.6, 68.9   2^18  96.2, 76.4
-static bool digits_pay(int64_t n) { return n > int64_t(1) << 16 && n <= kRadixMaxN; }
-
-// The digit sort of d's n elements, if it is the faster way and can be had:
-// false (nothing enqueued) for sizes the network sorts faster, on a stream
-// that is being captured (the graph would share the stream's workspace with
-// later calls), and where the workspace cannot be allocated.
-static bool sort_by_digits(const RadixData& d, int64_t n, hipStream_t st) {
-  const bool wide = d.keys64 || d.values;
-  if (!digits_pay(n)) return false;
+// The sort of d's n elements through a workspace, where that is the faster way
+// and it can be had: middle sizes by rank (rank_pays), longer arrays by digits.
+// False (nothing enqueued) for sizes the network sorts faster, for n = 2^31, on
+// a stream that is being captured (the graph would share the stream's workspace
+// with later calls), and where the workspace cannot be allocated.
+static bool sort_through_workspace(const RadixData& d, int64_t n, hipStream_t st) {
+  const int eb = d.keys64 || d.values ? 8 : 4;
+  if (n <= 1 << 11 || n > kRadixMaxN) return false;
+  const bool by_rank = rank_pays(n, eb, d.values != nullptr);
+  if (!by_rank && n <= 1 << 16) return false;
   int dev = 0;
   if (stream_is_capturing(st) || current_device(&dev) != BITONIC_OK) return false;
-  const size_t bytes = radix_space(nullptr, (uint32_t)n, wide ? 8 : 4, nullptr);
+  const size_t bytes =
+      by_rank ? rank_workspace_bytes(n, eb) : radix_space(nullptr, (uint32_t)n, eb, nullptr);
   void* const ws = g_workspaces.acquire(dev, st, bytes, st != hipStreamPerThread);
   if (!ws) return false;
-  launch_radix_sort(d, (uint32_t)n, ws, st);
+  if (by_rank)
+    launch_rank_sort(d, (uint32_t)n, ws, st);
+  else
+    launch_radix_sort(d, (uint32_t)n, ws, st);
   g_workspaces.release(dev, st, ws, bytes);
   return true;
 }
@@ -775,7 +775,7 @@ static int sort_wide(void* keys, int32_t* values, int64_t n, int key_type, int a
     } else {
       d.keys64 = static_cast<int64_t*>(keys);
     }
-    if (sort_by_digits(d, n, (hipStream_t)stream)) return finish_launches();
+    if (sort_through_workspace(d, n, (hipStream_t)stream)) return finish_launches();
   }
   if (pairs)
     enqueue_wide(nullptr, static_cast<int32_t*>(keys), values, (uint32_t)n, cd, L, F,
@@ -836,7 +836,7 @@ int bitonic_sort_keys(void* keys, int64_t n, int key_type, int ascending, void* 
     d.keys = k;
     d.cd = make_codec(key_type, ascending != 0);
     (void)hipGetLastError();
-    if (sort_by_digits(d, n, (hipStream_t)stream)) return finish_launches();
+    if (sort_through_workspace(d, n, (hipStream_t)stream)) return finish_launches();
   }
   fit_alignment(k, &r);
   rc = bind_device(&r);

@@ -14,13 +14,14 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-# Sizes: one above the route's start; the tiles' changes (4-byte 2^20 and
-# 2^22, 8-byte 2^19 and 2^20); a whole last tile, one element over and one
-# short; group (16 tiles) and supergroup (256 tiles) edges of the tile in use.
-SIZES32 = [(1 << 15) + 1, (1 << 16) + 1, 16 * 4096, 16 * 4096 + 1, (1 << 20) - 1, 1 << 20,
+# Sizes: one above the route's start (2^17 keys, 2^16 pairs); the tiles'
+# changes (4-byte 2^20 and 2^22, 8-byte 2^19 and 2^20); a whole last tile, one
+# element over and one short; group (16 tiles) and supergroup (256 tiles) edges
+# of the tile in use.
+SIZES32 = [(1 << 17) + 1, 48 * 4096, 48 * 4096 + 1, (1 << 20) - 1, 1 << 20,
            (1 << 20) + 1, 1 << 22, (1 << 22) + 1, (1 << 22) + 16 * 16384 - 1]
-SIZES64 = [(1 << 15) + 1, 16 * 2048 + 2048, (1 << 19) - 1, 1 << 19, (1 << 20) - 1, (1 << 20) + 1,
-           (1 << 21) + 1]
+SIZES64 = [(1 << 16) + 1, (1 << 17) + 1, 80 * 2048, (1 << 19) - 1, 1 << 19, (1 << 20) - 1,
+           (1 << 20) + 1, (1 << 21) + 1]
 
 
 def _bind():
@@ -148,7 +149,7 @@ def test_threads_and_streams():
     changing from call to call: each result is the array's own."""
     B = _bind()
     shared = torch.cuda.Stream()
-    sizes = [70_001, 1 << 20, 200_000, 3_000_001]
+    sizes = [70_001, 1 << 20, 200_000, 3_000_001]  # the first by rank
     keys = [[W.uniform_i32(900 + 10 * t + i, n) for i, n in enumerate(sizes)] for t in range(4)]
     got = [[None] * len(sizes) for _ in range(4)]
 
