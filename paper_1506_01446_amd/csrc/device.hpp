@@ -300,6 +300,28 @@ __device__ __forceinline__ uint32_t slot_index(uint32_t base) {
   return base + goff(gr, J);
 }
 
+// A thread's N elements of a partly filled tile: get(index(J)) mapped into the
+// sorting domain, or the sentinel where index(J) is `valid` or above.  All
+// loads are issued (those above at element 0, which is there) before the first
+// one's element is mapped: with the mapping under each load's own condition the
+// compiler waits for every load before the next, and 8 to 32 latencies of
+// memory follow each other (MI355X, 8192 segments of 48.7 M pairs: passes of
+// three steps 150 -> 90 us and of two 192 -> 148, the whole sort 1604 -> 1436;
+// 2^14 8-byte keys by rank 16.3 -> 14.0).
+template <int N, class E, class I, class G, class CD>
+__device__ __forceinline__ void load_checked(E (&x)[N], uint32_t valid, I index, G get, CD cd,
+                                             E pad) {
+  if (valid != 0) {
+    static_for<0, N>([&](auto J) {
+      const uint32_t i = index(J);
+      x[J] = get(i < valid ? i : 0u);
+    });
+  } else {
+    static_for<0, N>([&](auto J) { x[J] = pad; });
+  }
+  static_for<0, N>([&](auto J) { x[J] = index(J) < valid ? cd.enc(x[J]) : pad; });
+}
+
 // Load the thread's keys of a tile in the layout of group G.
 // `valid` keys of the tile exist; the rest read as the sentinel.
 template <class PR, int G, class CD>
@@ -322,10 +344,8 @@ __device__ __forceinline__ void load_tile(int32_t (&x)[PR::R], const int32_t* __
       static_for<0, PR::R>([&](auto J) { x[J] = cd.enc(tile[slot_index<PR, G, J>(base)]); });
     }
   } else {
-    static_for<0, PR::R>([&](auto J) {
-      const uint32_t i = slot_index<PR, G, J>(base);
-      x[J] = i < valid ? cd.enc(tile[i]) : kPad;
-    });
+    load_checked(x, valid, [&](auto J) { return slot_index<PR, G, J>(base); },
+                 [&](uint32_t i) { return tile[i]; }, cd, kPad);
   }
 }
 

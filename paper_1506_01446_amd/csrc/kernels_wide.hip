@@ -57,10 +57,8 @@ __global__ __launch_bounds__(1 << (L - RL)) void wide_tile_kernel(ST st, uint32_
     if (full) {
       static_for<0, PR::R>([&](auto J) { x[J] = cd.enc(tile.get(slot_index<PR, 0, J>(base))); });
     } else {
-      static_for<0, PR::R>([&](auto J) {
-        const uint32_t i = slot_index<PR, 0, J>(base);
-        x[J] = i < valid ? cd.enc(tile.get(i)) : kPad64;
-      });
+      load_checked(x, valid, [&](auto J) { return slot_index<PR, 0, J>(base); },
+                   [&](uint32_t i) { return tile.get(i); }, cd, kPad64);
     }
   }
   if constexpr (SPLIT)

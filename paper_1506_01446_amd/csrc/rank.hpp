@@ -17,7 +17,7 @@ namespace bitonic {
 // at most 16 tiles, within the sizes that pay.  A larger tile takes the first
 // launch longer (2^10, 2^11, 2^12 8-byte elements 8, 10, 16 us), more tiles
 // the second one, whose searches are elements times tiles.  Whole sorts on
-// MI355X in us, by tile (2^13 4-byte keys at 16 a thread, else 8):
+// MI355X in us, by tile (all of them 1.5 to 2 us less with load_checked) (2^13 4-byte keys at 16 a thread, else 8):
 //   4-byte keys  2^14  2^10 10.9, 2^11 10.3    2^15  13.9, 12.0, 2^12 12.9
 //                2^16  2^11 20.5, 2^12 17.8    2^17  2^12 37.0, 2^13 32.7
 //   8-byte keys  2^12  2^9 12.8, 2^10 13.8     2^13  14.1, 13.7
@@ -33,10 +33,10 @@ constexpr int rank_tile_log2(int64_t n, int elem_bytes) {
 // Whether n elements are sorted this way: more than one launch of the network
 // sorts (4-byte keys 2^12, 8-byte elements 2^11), and fewer than the digit
 // sort is faster for.  Measured in us, rank against digits:
-//   4-byte keys  70000  26.1, 37.0    100000  32.1, 37.2    2^17  35.9, 37.7
-//   8-byte keys  70000  36.7, 61.5    100000  43.6, 63.2    2^17  49.3, 64.3
-//   pairs        2^16   29.7, 43.3 (values in order), 62.7
-//                2^17   59.0, 45.5 and 66.6
+//   4-byte keys  70000  22.5, 37.0    100000  28.2, 37.2    2^17  32.1, 37.7
+//   8-byte keys  70000  35.6, 61.5    100000  42.2, 63.2    2^17  48.0, 64.3
+//   pairs        2^16   28.0, 43.3 (values in order), 62.7
+//                2^17   57.5, 45.5 and 66.6
 constexpr bool rank_pays(int64_t n, int elem_bytes, bool pairs) {
   return n > (elem_bytes == 4 ? 1 << 12 : 1 << 11) && n <= (pairs ? 1 << 16 : 1 << 17);
 }

@@ -7,11 +7,11 @@
 // every element does the merges' work in one launch whose longest chain is
 // seven reads of LDS and six of memory, at a cost in reads (elements x tiles)
 // that the idle chip has.  Whole sorts on MI355X in us, network against rank:
-//   4-byte keys  5000  12.5, 8.6    2^14  15.9, 10.9    20000  28.5, 11.4
-//                2^15  22.5, 12.0   50000 35.0, 16.4    2^16   28.1, 17.8
-//   8-byte keys  2^12  16.5, 12.8   2^13  24.0, 14.1    2^14   31.7, 16.3
-//                2^15  40.3, 18.4   50000 53.0, 24.9    2^16   52.2, 26.9
-//   pairs        2^13  23.5, 14.4   2^15  39.4, 19.6    2^16   51.1, 29.8
+//   4-byte keys  5000  12.5, 7.6    2^14  15.9, 8.9     20000  28.5, 9.2
+//                2^15  22.5, 10.3   50000 35.0, 14.9    2^16   28.1, 16.1
+//   8-byte keys  2^12  16.5, 11.0   2^13  24.0, 11.6    2^14   31.7, 13.9
+//                2^15  40.3, 17.0   50000 53.0, 25.1    2^16   52.2, 26.4
+//   pairs        2^13  23.5, 12.2   2^15  39.4, 17.8    2^16   51.1, 28.0
 #pragma once
 
 #include "column_pass.hpp"
@@ -36,10 +36,8 @@ __global__ __launch_bounds__(1 << (L - RL)) void rank_tile_kernel(ST src, ST dst
   E x[PR::R];
   {
     const uint32_t base = deposit<free_mask(PR::value.g[0], L)>(tid);
-    static_for<0, PR::R>([&](auto J) {
-      const uint32_t i = slot_index<PR, 0, J>(base);
-      x[J] = i < valid ? cd.enc(in.get(i)) : ST::kPadE;
-    });
+    load_checked(x, valid, [&](auto J) { return slot_index<PR, 0, J>(base); },
+                 [&](uint32_t i) { return in.get(i); }, cd, ST::kPadE);
   }
   run_from<PR, 0>(x, lds, tid);
   asm volatile("" : "+v"(tid));  // the bases are computed anew: fewer registers

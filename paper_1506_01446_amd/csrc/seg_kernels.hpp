@@ -51,10 +51,8 @@ __device__ __forceinline__ void seg_tile_program(ST tile, uint32_t valid, CD cd,
       if (full) {
         static_for<0, PR::R>([&](auto J) { x[J] = cd.enc(tile.get(slot_index<PR, 0, J>(base))); });
       } else {
-        static_for<0, PR::R>([&](auto J) {
-          const uint32_t i = slot_index<PR, 0, J>(base);
-          x[J] = i < valid ? cd.enc(tile.get(i)) : ST::kPadE;
-        });
+        load_checked(x, valid, [&](auto J) { return slot_index<PR, 0, J>(base); },
+                     [&](uint32_t i) { return tile.get(i); }, cd, ST::kPadE);
       }
     }
     if constexpr (SPLIT)
@@ -467,12 +465,9 @@ __global__ __launch_bounds__(kSegThreads) void seg_pass_kernel(
     const uint32_t blk = (lu >> upb_log) << (q + F);
     const uint32_t c0 = (lu & ((1u << upb_log) - 1u)) << COL_LOG;
     typename ST::E x[COLS * ROWS];
-    static_for<0, ROWS>([&](auto RHO) {
-      static_for<0, COLS>([&](auto J) {
-        const uint32_t idx = seg_pass_index<F, MIRROR, RHO, J>(blk, c0, q);
-        x[COLS * RHO + J] = idx < len ? cd.enc(a.get(idx)) : ST::kPadE;
-      });
-    });
+    load_checked(x, len,
+                 [&](auto S) { return seg_pass_index<F, MIRROR, S / COLS, S % COLS>(blk, c0, q); },
+                 [&](uint32_t idx) { return a.get(idx); }, cd, ST::kPadE);
     pass_steps<F, MIRROR, COLS>(x);
     static_for<0, ROWS>([&](auto RHO) {
       static_for<0, COLS>([&](auto J) {
