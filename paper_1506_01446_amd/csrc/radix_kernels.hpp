@@ -92,11 +92,27 @@ __device__ __forceinline__ void radix_count(RadixBinsLds<ST>& lds, const MAP& ma
     static_for<0, U>([&](auto J) { x[J] = a.get((uint32_t)(i + J * NT)); });
     static_for<0, U>([&](auto J) { count(x[J]); });
   }
-  for (; i < hi; i += NT) count(a.get((uint32_t)i));
+  if (i < hi) {
+    E x[U];
+    static_for<0, U>([&](auto J) { x[J] = a.get((uint32_t)(i + J * NT < hi ? i + J * NT : i)); });
+    static_for<0, U>([&](auto J) {
+      if (i + J * NT < hi) count(x[J]);
+    });
+  }
   if constexpr (std::is_same_v<ST, Pairs>) {
+    // U comparisons' loads in flight, those past the end at the first one's
+    // place (one at a time the loop took longer than the counting)
     bool down = false;
-    for (uint64_t j = lo + tid; j < hi; j += NT)
-      down = down || (j + 1 < n && a.v[j] > a.v[j + 1]);
+    const uint64_t last = hi < n ? hi : n - 1;  // j + 1 < n
+    for (uint64_t j = lo + tid; j < last; j += U * NT) {
+      int32_t v[U], w[U];
+      static_for<0, U>([&](auto J) {
+        const uint64_t at = j + J * NT < last ? j + J * NT : j;
+        v[J] = a.v[at];
+        w[J] = a.v[at + 1];
+      });
+      static_for<0, U>([&](auto J) { down |= v[J] > w[J]; });
+    }
     if (down) lds.decrease = 1;
   }
   __syncthreads();
@@ -305,8 +321,12 @@ __device__ __forceinline__ void radix_tile(RadixLds<typename MAP::U, IPT>& lds, 
     static_for<0, IPT>([&](auto I) { x[I] = (U)src.getb((first + 64u * I) * ST::kUnit); });
     static_for<0, IPT>([&](auto I) { x[I] = map.enc((typename ST::E)x[I]); });
   } else {
+    // every load before the first use (load_checked); valid > 0
     static_for<0, IPT>([&](auto I) {
-      x[I] = first + 64u * I < valid ? map.enc(src.get(first + 64u * I)) : ~(U)0;
+      x[I] = (U)src.get(first + 64u * I < valid ? first + 64u * I : 0u);
+    });
+    static_for<0, IPT>([&](auto I) {
+      x[I] = first + 64u * I < valid ? map.enc((typename ST::E)x[I]) : ~(U)0;
     });
   }
   // this tile's rows of the next executed pass
