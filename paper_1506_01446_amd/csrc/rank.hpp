@@ -17,7 +17,8 @@ namespace bitonic {
 // at most 16 tiles, within the sizes that pay.  A larger tile takes the first
 // launch longer (2^10, 2^11, 2^12 8-byte elements 8, 10, 16 us), more tiles
 // the second one, whose searches are elements times tiles.  Whole sorts on
-// MI355X in us, by tile (all of them 1.5 to 2 us less with load_checked) (2^13 4-byte keys at 16 a thread, else 8):
+// MI355X in us, by tile, before load_checked took 1.5 to 2 us off each (2^13
+// 4-byte keys at 16 a thread, else 8):
 //   4-byte keys  2^14  2^10 10.9, 2^11 10.3    2^15  13.9, 12.0, 2^12 12.9
 //                2^16  2^11 20.5, 2^12 17.8    2^17  2^12 37.0, 2^13 32.7
 //   8-byte keys  2^12  2^9 12.8, 2^10 13.8     2^13  14.1, 13.7

@@ -160,8 +160,7 @@ __global__ __launch_bounds__(kSegRadixHistThreads) void segradix_scan_kernel(
   const uint32_t id = big_ids[i];
   const uint32_t len = (uint32_t)(offsets[id + 1] - offsets[id]);
   const uint64_t tiles = big_tiles[seg_meta->nradix];
-  const uint64_t per = (tiles + gridDim.x - 1) / gridDim.x;  // unit_range
-  const uint32_t last = (uint32_t)((big_tiles[i + 1] - 1) / per);
+  const uint32_t last = unit_owner(tiles, big_tiles[i + 1] - 1);
   // row 1 of the first range, row 0 of the others
   auto row = [&](uint32_t r) { return (blockIdx.x + r) * 2 + (r == 0 ? 1u : 0u); };
   const uint32_t rows = last - blockIdx.x + 1;
