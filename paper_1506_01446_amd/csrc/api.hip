@@ -492,6 +492,7 @@ static bool sort_through_workspace(const RadixData& d, int64_t n, hipStream_t st
       by_rank ? rank_workspace_bytes(n, eb) : radix_space(nullptr, (uint32_t)n, eb, nullptr);
   void* const ws = g_workspaces.acquire(dev, st, bytes, st != hipStreamPerThread);
   if (!ws) return false;
+  (void)hipGetLastError();
   if (by_rank)
     launch_rank_sort(d, (uint32_t)n, ws, st);
   else
@@ -835,7 +836,6 @@ int bitonic_sort_keys(void* keys, int64_t n, int key_type, int ascending, void* 
     RadixData d{};
     d.keys = k;
     d.cd = make_codec(key_type, ascending != 0);
-    (void)hipGetLastError();
     if (sort_through_workspace(d, n, (hipStream_t)stream)) return finish_launches();
   }
   fit_alignment(k, &r);
