@@ -420,7 +420,7 @@ int64_t bitonic_plan_describe(int64_t n, const bitonic_plan* plan, int32_t* kind
  * segmented sorts BITONIC_LAYOUT_SEG_KEYS32, BITONIC_LAYOUT_SEG_PAIRS,
  * BITONIC_LAYOUT_SEG_KEYS64, whose longest segment holds n elements (the
  * bound of bitonic_sort_segmented_bounded_i32).  The network's launches, for
- * sizes that go by digits too.  Returns the number of
+ * sizes that go by rank or digits too.  Returns the number of
  * launches, or -1 for a bad argument (n < 0, n > 2^31, a bad plan or layout).
  */
 typedef struct bitonic_launch_shape {

@@ -1,4 +1,4 @@
-// Workspaces of the digit sorts (host code, no HIP: the allocator is a
+// Workspaces of the digit and rank sorts (host code, no HIP: the allocator is a
 // parameter, so the policy is tested on the CPU).
 //
 // A sort on stream S takes S's buffer.  Work on one stream is ordered, so the
