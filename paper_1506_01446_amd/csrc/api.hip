@@ -1086,8 +1086,9 @@ static int sort_segmented(void* keys_v, int32_t* values, const int64_t* offsets,
   size_t ws_bytes = 0;
   const int eb = d.keys64 || d.values ? 8 : 4;
   const int64_t elems = segmented_elems(keys_v, wide_keys ? 8 : 4, nseg, max_seg_len);
-  if (ceil_log2(max_seg_len) >= seg_radix_min_bound(tight, eb == 8) &&
-      elems <= kSegRadixMaxElems) {
+  // no segment is longer than all of them together, however loose its bound
+  const int64_t longest = max_seg_len < elems ? max_seg_len : elems;
+  if (ceil_log2(longest) >= seg_radix_min_bound(tight, eb == 8) && elems <= kSegRadixMaxElems) {
     ws_bytes = segradix_space(nullptr, elems, nseg, eb, nullptr);
     ws = g_workspaces.acquire(dev, st, ws_bytes, st != hipStreamPerThread);
     if (ws) segradix_space(static_cast<char*>(ws), elems, nseg, eb, &digits);
