@@ -208,14 +208,15 @@ int bitonic_validation_error(int32_t* code);
 int64_t bitonic_segmented_default_bound(const void* keys, int key_bytes);
 
 /*
- * Segments of more than 2^13 elements go by their digits, as long single
- * arrays do, when the longest has more than 2^17 (with a bound: when the
- * bound is above that; without one: in allocations of more than 2^20 4-byte
- * or 2^22 8-byte elements).  The workspace, as of a single array as long as all
+ * Segments of more than 2^17 elements go by their digits, as long single
+ * arrays do, when the bound (or what stands for it, see below) is above 2^19
+ * and the elements in all may be; if those of 2^13 + 1 to 2^17 elements are
+ * few they go with them, otherwise the network sorts them as it does without
+ * any longer one.  The workspace, as of a single array as long as all
  * segments together, is laid out for the smaller of nseg * max_seg_len and
  * the elements from `keys` to the end of their allocation, by the runtime's
  * records; where that is more than 2^28 elements, or cannot be had, the
- * network sorts them.  (bitonic_sort_segmented_noalloc_i32 and graphs always
+ * network sorts all.  (bitonic_sort_segmented_noalloc_i32 and graphs always
  * run the network.)
  *
  * As bitonic_sort_segmented_i32, with a host-side bound: every segment holds
@@ -223,10 +224,12 @@ int64_t bitonic_segmented_default_bound(const void* keys, int key_bytes);
  * bitonic_sort_segmented_i32 is taken).  The bound fixes how many merge
  * phases are enqueued; a segment longer than the bound is undefined
  * behaviour.  Launches: a prep kernel, one persistent kernel for all segments
- * of up to 2^13 keys, and, if the bound exceeds 2^13, those of the digit sort
- * (one per digit and two) or, by the network, one tile-sort launch
+ * of up to 2^13 keys, and, if the bound exceeds 2^13, one tile-sort launch
  * plus, per phase p = 14 .. ceil(log2 bound), its fused long-stride passes
- * (at most "seg_fuse" steps each, default 5) and one tile merge.  Like
+ * (at most "seg_fuse" steps each, default 5) and one tile merge; with the
+ * digit sort its launches (one per digit and two) take the place of the
+ * phases above 17.  Launches that find no segment of theirs take 2 to 2.5
+ * microseconds each.  Like
  * bitonic_sort_segmented_i32 it refuses a capturing stream.
  */
 int bitonic_sort_segmented_bounded_i32(int32_t* keys, const int64_t* offsets,

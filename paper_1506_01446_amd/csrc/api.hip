@@ -518,27 +518,6 @@ static int seg_tile_log_of(const SegData& d) {
   return (d.keys64 || d.values) ? kSegTileLog64 : kSegTileLog32;
 }
 
-// The least class (log2 of the padded length) of the longest segment that
-// makes the digit sort of the big segments (segradix.hpp) the faster way.
-// Measured on MI355X in us, network against digits, with the longest segment
-// of class 16, 17, 18 and 20:
-//   int32    4 segments   61, 97     82, 98     109, 101   222, 113
-//           32 segments   74, 111   119, 124    175, 155   709, 347
-//   int64    4 segments  115, 130   142, 135    178, 147   334, 223
-//           32 segments  142, 183   207, 227    370, 321  1706, 1087
-//   pairs   32 segments  146, 148   214, 195    379, 280  1687, 888
-// (pairs with values in order; others as int64).
-constexpr int kSegRadixMinClass = 18;
-
-// Without a bound on the segments both ways are launched and the device
-// leaves one of them idle, at about 3 us a launch: from this class of the
-// allocation's bound on, the network's launches up to class 17 and the digit
-// sort's (4-byte keys 6 + 6, 8-byte elements 8 + 10) are fewer than the
-// network's up to the bound.
-static int seg_radix_min_bound(bool tight, bool wide) {
-  return tight ? kSegRadixMinClass : (wide ? 23 : 21);
-}
-
 // The launch sequence of one segmented sort (see kernels_segmented.hip) on
 // the given scratch buffer (seg_scratch_bytes(nseg) bytes); returns the
 // number of launches (enqueued unless count_only; shapes to obs, with `unit`
@@ -547,8 +526,7 @@ static int seg_radix_min_bound(bool tight, bool wide) {
 static int64_t enqueue_segmented(const SegData& d, const int64_t* offsets, int64_t nseg,
                                  int64_t max_seg_len, void* scratch, int cus, hipStream_t st,
                                  bool count_only = false, Observer* obs = nullptr,
-                                 int unit = 4, const SegRadixSpace* digits = nullptr,
-                                 bool tight = true) {
+                                 int unit = 4, const SegRadixSpace* digits = nullptr) {
   const int T = seg_tile_log_of(d);
   int64_t launches = 0;
   auto emit = [&](bitonic_launch_shape sh, auto&& launch) {
@@ -561,12 +539,8 @@ static int64_t enqueue_segmented(const SegData& d, const int64_t* offsets, int64
   // not counted among the sort's launches)
   const bool validated = !count_only && validate_enabled();
   if (validated) launch_seg_validate(offsets, nseg, max_seg_len, sc, st);
-  // digits with a tight bound: the big segments go by digits.  Without one the
-  // device decides by the largest segment, and the network's launches for
-  // smaller ones are there too.
-  const int radix_cls = !digits ? 0 : (tight ? kSegSmallMaxLog2 + 1 : kSegRadixMinClass);
   emit({BITONIC_LAUNCH_SEG_PREP, 0, 0, 0, unit, 64}, [&] {
-    launch_seg_prep(offsets, nseg, sc, T, validated, radix_cls,
+    launch_seg_prep(offsets, nseg, sc, T, validated,
                     digits ? &digits->meta->trivial[0] : nullptr, st);
   });
   const bool few = seg_small_few(nseg, ceil_log2(max_seg_len), T == kSegTileLog64);
@@ -578,7 +552,6 @@ static int64_t enqueue_segmented(const SegData& d, const int64_t* offsets, int64
   if (M <= kSegSmallMaxLog2) return launches;
   if (digits) {
     launch_segradix(d, offsets, sc, *digits, cus, st);
-    if (tight) return launches;
     M = kSegRadixMinClass - 1;
   }
   // two workgroups per CU of the 2^14-key tiles (67.6 KB of LDS each), four
@@ -1036,10 +1009,6 @@ static int64_t segmented_elems(const void* keys, int elem_bytes, int64_t nseg,
   return in_allocation < by_length ? in_allocation : by_length;
 }
 
-// The most elements (by that bound, not by what the segments hold) that a
-// segmented sort takes a digit workspace for: 1 GiB of 4-byte keys.
-constexpr int64_t kSegRadixMaxElems = int64_t(1) << 28;
-
 // Segmented sort of keys of any key type (values == nullptr) or of (key,
 // value) pairs with 4-byte keys.
 static int sort_segmented(void* keys_v, int32_t* values, const int64_t* offsets, int64_t nseg,
@@ -1061,11 +1030,7 @@ static int sort_segmented(void* keys_v, int32_t* values, const int64_t* offsets,
   int dev = 0;
   int rc = current_device(&dev);
   if (rc) return rc;
-  const int64_t available = allocation_bound(keys_v, wide_keys ? 8 : 4);
-  // a bound that several segments cannot all come near says little about
-  // them: it is then the size of the keys' memory, or as good as that
-  const bool tight = max_seg_len != 0 && (nseg == 1 || max_seg_len < available / 2);
-  if (max_seg_len == 0) max_seg_len = available;
+  if (max_seg_len == 0) max_seg_len = allocation_bound(keys_v, wide_keys ? 8 : 4);
   void* base = nullptr;
   rc = stream_scratch(dev, st, seg_scratch_bytes(nseg), &base);
   if (rc) return rc;
@@ -1086,15 +1051,13 @@ static int sort_segmented(void* keys_v, int32_t* values, const int64_t* offsets,
   size_t ws_bytes = 0;
   const int eb = d.keys64 || d.values ? 8 : 4;
   const int64_t elems = segmented_elems(keys_v, wide_keys ? 8 : 4, nseg, max_seg_len);
-  // no segment is longer than all of them together, however loose its bound
-  const int64_t longest = max_seg_len < elems ? max_seg_len : elems;
-  if (ceil_log2(longest) >= seg_radix_min_bound(tight, eb == 8) && elems <= kSegRadixMaxElems) {
+  if (seg_digit_launches(max_seg_len, elems)) {
     ws_bytes = segradix_space(nullptr, elems, nseg, eb, nullptr);
     ws = g_workspaces.acquire(dev, st, ws_bytes, st != hipStreamPerThread);
     if (ws) segradix_space(static_cast<char*>(ws), elems, nseg, eb, &digits);
   }
   enqueue_segmented(d, offsets, nseg, max_seg_len, base, device_cus(dev), st, false, nullptr, 4,
-                    ws ? &digits : nullptr, tight);
+                    ws ? &digits : nullptr);
   if (ws) g_workspaces.release(dev, st, ws, ws_bytes);
   return finish_launches();
 }

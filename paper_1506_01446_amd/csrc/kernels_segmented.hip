@@ -77,7 +77,7 @@ __global__ __launch_bounds__(1024) void seg_prep_kernel(const int64_t* __restric
                                                         uint32_t* __restrict__ big_ids,
                                                         uint64_t* __restrict__ big_keys,
                                                         uint64_t* __restrict__ big_tiles,
-                                                        int tile_log, int validated, int radix_cls,
+                                                        int tile_log, int validated,
                                                         uint32_t* __restrict__ any_unordered) {
   __shared__ uint32_t cnt[32];
   __shared__ uint32_t cur[32];
@@ -149,20 +149,19 @@ __global__ __launch_bounds__(1024) void seg_prep_kernel(const int64_t* __restric
     meta->small_items = items;
     meta->small_counter = 0;
     // big buckets, largest class first
-    uint32_t bpos = 0;
+    const int digit_cls = any_unordered ? seg_digit_class(cnt) : 32;
+    uint32_t bpos = 0, nradix = 0;
     int maxc = 0;
     for (int c = 31; c > kSegSmallMaxLog2; --c) {
       cur[c] = bpos;
       bpos += cnt[c];
       meta->big_ge[c] = bpos;  // segments of class >= c
+      if (c == digit_cls) nradix = bpos;
       if (cnt[c] && !maxc) maxc = c;
     }
     for (int c = 0; c <= kSegSmallMaxLog2; ++c) meta->big_ge[c] = bpos;
     meta->big_ge[32] = 0;
-    const bool radix = radix_cls != 0 && maxc >= radix_cls;
-    meta->nradix = radix ? bpos : 0;
-    if (radix)
-      for (int c = 0; c < 32; ++c) meta->big_ge[c] = 0;
+    meta->nradix = nradix;
     meta->nbig = bpos;
     meta->max_class = maxc;
     nbig_s = bpos;
@@ -232,10 +231,10 @@ static void seg_dispatch(const SegData& d, const SegLaunch& l, const int64_t* of
 }
 
 void launch_seg_prep(const int64_t* offsets, int64_t nseg, const SegScratch& sc, int tile_log,
-                     bool validated, int radix_cls, uint32_t* any_unordered, hipStream_t st) {
+                     bool validated, uint32_t* any_unordered, hipStream_t st) {
   seg_prep_kernel<<<1, 1024, 0, st>>>(offsets, nseg, sc.meta, sc.small_ids, sc.big_ids,
                                       sc.big_keys, sc.big_tiles, tile_log, validated ? 1 : 0,
-                                      radix_cls, any_unordered);
+                                      any_unordered);
 }
 
 void launch_seg_small(const SegData& d, const int64_t* offsets, const SegScratch& sc, int grid,

@@ -196,6 +196,25 @@ __device__ __forceinline__ uint32_t unit_owner(uint64_t total, uint64_t u) {
   return (uint32_t)(u < more * (per + 1) ? u / (per + 1) : more + (u - more * (per + 1)) / per);
 }
 
+// The big segments of class >= cls that the network sorts: places first to
+// end of the list (those before first go by digits).
+struct BigRange {
+  uint32_t first, end;
+};
+__device__ __forceinline__ BigRange network_segments(const SegMeta* __restrict__ meta, int cls) {
+  const uint32_t first = meta->nradix, end = meta->big_ge[cls];
+  return BigRange{first, end > first ? end : first};
+}
+// unit_range of their units of 2^unit_log elements, given the prefix sums of
+// the segments' sizes (of digits' segments whole units).
+__device__ __forceinline__ void network_units(const uint64_t* __restrict__ prefix, BigRange r,
+                                              int unit_log, uint64_t* first, uint64_t* end) {
+  const uint64_t u0 = prefix[r.first] >> unit_log;
+  unit_range((prefix[r.end] >> unit_log) - u0, first, end);
+  *first += u0;
+  *end += u0;
+}
+
 // upper_index(prefix, cnt, v) given i = upper_index(prefix, cnt, v') for some
 // v' <= v.
 __device__ __forceinline__ uint32_t advance_index(const uint64_t* __restrict__ prefix,
@@ -234,9 +253,10 @@ __global__ __launch_bounds__(seg_tile_threads<ST>()) void seg_tile_kernel(
   constexpr bool SPLIT = sizeof(typename ST::E) == 8;
   __shared__ uint32_t lds32[PR::LDSW * (SPLIT ? 1 : sizeof(typename ST::E) / 4)];
   typename ST::E* lds = reinterpret_cast<typename ST::E*>(lds32);
-  const uint32_t cnt = meta->big_ge[cls_min];
+  const BigRange range = network_segments(meta, cls_min);
+  const uint32_t cnt = range.end;
   uint64_t u, uend;
-  unit_range(big_tiles[cnt], &u, &uend);
+  network_units(big_tiles, range, 0, &u, &uend);
   uint32_t i = u < uend ? upper_index(big_tiles, cnt, u) : 0u;
   // tile uu's first element (segment-relative start off + t0) and its real
   // element count; i walks forward through the big-segment list
@@ -348,9 +368,10 @@ __global__ __launch_bounds__(seg_phase_threads<ST>()) void seg_phase_kernel(
   __shared__ uint32_t lds32[PR::LDSW];
   constexpr Group g0 = PR::value.g[0];
   constexpr int LAST = PR::value.ngroups - 1;
-  const uint32_t cnt = meta->big_ge[kSegPhaseLog];
+  const BigRange range = network_segments(meta, kSegPhaseLog);
+  const uint32_t cnt = range.end;
   uint64_t u, uend;
-  unit_range(big_keys[cnt] >> kSegPhaseLog, &u, &uend);
+  network_units(big_keys, range, kSegPhaseLog, &u, &uend);
   uint32_t i = u < uend ? upper_index(big_keys, cnt, u << kSegPhaseLog) : 0u;
   // unit uu's first element and real element count; false for a unit of
   // padding only (the same answer for the whole workgroup)
@@ -453,9 +474,10 @@ __global__ __launch_bounds__(kSegThreads) void seg_pass_kernel(
   constexpr int COLS = seg_pass_cols(F);
   constexpr int COL_LOG = 8 + seg_pass_cols_log(F);  // columns per unit, log2
   constexpr int UNIT_LOG = COL_LOG + F;              // elements per unit, log2
-  const uint32_t cnt = meta->big_ge[cls];
+  const BigRange range = network_segments(meta, cls);
+  const uint32_t cnt = range.end;
   uint64_t u, uend;
-  unit_range(big_keys[cnt] >> UNIT_LOG, &u, &uend);
+  network_units(big_keys, range, UNIT_LOG, &u, &uend);
   uint32_t i = u < uend ? upper_index(big_keys, cnt, u << UNIT_LOG) : 0u;
   for (; u < uend; ++u) {
     const uint64_t key0 = u << UNIT_LOG;

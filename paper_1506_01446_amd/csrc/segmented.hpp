@@ -5,11 +5,11 @@
 #include <stdint.h>
 
 #include "codec.hpp"
+#include "segroute.hpp"
 
 namespace bitonic {
 
 constexpr int kTileRegLogSeg = 5;  // 32 keys per thread
-constexpr int kSegSmallMaxLog2 = 13;  // segments of up to 2^13 keys are "small"
 // Tiles of the big segments: 2^14 4-byte keys (the single-array sort's tile,
 // 67.6 KB of LDS, two workgroups per CU), 2^13 8-byte elements (regrouped
 // through half the LDS, 34 KB, four per CU).
@@ -29,7 +29,7 @@ struct SegMeta {
   uint32_t item_prefix[kSmallClasses + 1];
   uint32_t big_ge[33];     // number of big segments of class >= c
   int32_t invalid;         // set by the validation kernel: the table is refused
-  uint32_t nradix;         // big segments that go by digits: all of them or none
+  uint32_t nradix;         // big segments that go by digits: the first of big_ids
 };
 static_assert(sizeof(SegMeta) <= 1024, "the segment meta block takes the scratch's first KiB");
 
@@ -133,13 +133,13 @@ void seg_run_keys64(const SegData& d, const SegLaunch& l, const int64_t* offsets
                     const SegScratch& sc, hipStream_t st);
 
 // tile_log: log2 of the big segments' tile (kSegTileLog32 or kSegTileLog64).
-// radix_cls: the big segments go by digits (segradix.hpp) if the largest is
-// of that class or above, and the network's kernels then find none (0: the
-// network in any case).  any_unordered: a word of the digit sort to clear.
+// any_unordered: digit launches follow (segradix.hpp), so the big segments of
+// seg_digit_class and above are left to them and not to the network's; a word
+// of the digit sort to clear.  nullptr: the network takes all.
 // validated: a validation kernel ran first (launch_seg_validate); an invalid
 // table then classifies as empty, so no later kernel touches the keys.
 void launch_seg_prep(const int64_t* offsets, int64_t nseg, const SegScratch& sc, int tile_log,
-                     bool validated, int radix_cls, uint32_t* any_unordered, hipStream_t st);
+                     bool validated, uint32_t* any_unordered, hipStream_t st);
 
 // Checks offsets[0 .. nseg] (nondecreasing, offsets[0] >= 0, every segment
 // below 2^31 keys and at most `bound` keys) on the device; records the first

@@ -1,0 +1,61 @@
+// Checks the routing of segmented sorts (csrc/segroute.hpp) on the host;
+// prints "ok", or the failed check.
+#include <cstdio>
+
+#include "../paper_1506_01446_amd/csrc/segroute.hpp"
+
+using namespace bitonic;
+
+#define CHECK(c)                                  \
+  do {                                            \
+    if (!(c)) {                                   \
+      std::printf("line %d: %s\n", __LINE__, #c); \
+      return 1;                                   \
+    }                                             \
+  } while (0)
+
+int main() {
+  // the bound alone never brings the digit launches: they need elements for
+  // at least one long segment, and a bound as far up as they are worth it
+  for (int b = 0; b <= 31; ++b)
+    for (int e = 0; e <= 40; ++e)
+      for (int64_t d = -1; d <= 1; ++d) {
+        const int64_t bound = (int64_t(1) << b) + (b < 31 ? d : 0), elems = (int64_t(1) << e) + d;
+        if (!seg_digit_launches(bound, elems)) continue;
+        CHECK(bound > int64_t(1) << 19 && elems > int64_t(1) << 19);
+        CHECK(elems <= kSegRadixMaxElems);
+      }
+  CHECK(seg_digit_launches(int64_t(1) << 22, 11000000));
+  CHECK(!seg_digit_launches(1 << 18, int64_t(1) << 25));
+  {  // no segment above 2^17: none by digits, whatever the bound was
+    uint32_t cnt[32] = {};
+    for (int c = 0; c <= 17; ++c) cnt[c] = 1000;
+    CHECK(seg_digit_class(cnt) == 32);
+    // one long one among many of the middle classes: it alone
+    for (int c = 18; c <= 31; ++c) {
+      cnt[c] = 1;
+      CHECK(seg_digit_class(cnt) == kSegRadixMinClass);
+      cnt[c] = 0;
+    }
+  }
+  {  // few of the middle classes go with the long ones, as many do not
+    for (int c = 14; c <= 17; ++c) {
+      uint32_t cnt[32] = {};
+      cnt[13] = 100000;
+      cnt[20] = 2;
+      cnt[c] = (uint32_t)(kSegRadixMaxMedium >> c);
+      CHECK(seg_digit_class(cnt) == 14);
+      cnt[c] += 1;
+      CHECK(seg_digit_class(cnt) == kSegRadixMinClass);
+      cnt[20] = 0;
+      CHECK(seg_digit_class(cnt) == 32);
+    }
+    uint32_t cnt[32] = {};
+    CHECK(seg_digit_class(cnt) == 32);
+    cnt[17] = 0xFFFFFFFFu;  // no wrap
+    cnt[18] = 1;
+    CHECK(seg_digit_class(cnt) == kSegRadixMinClass);
+  }
+  std::printf("ok\n");
+  return 0;
+}

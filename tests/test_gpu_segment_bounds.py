@@ -42,3 +42,76 @@ def test_small_arrays_with_loose_bounds(type_, lens, bound_log2):
         want[a:b] = O.sort_keys64(k[a:b].view(type_), 5, False).view(np.int64) if wide else \
             O.sort_i32(k[a:b], False)
     assert np.array_equal(t.cpu().numpy(), want)
+
+
+# Segments for the network (classes 14 to 17), for the digits (18 and above)
+# and for neither (2^13 and below), with the long ones first, last and
+# between; "many" has enough of the middle classes for the network to keep
+# them beside the digits' launches, "few" has not, "none" has no long one.
+TABLES = {
+    "many": [(1 << 18) + 1, 0, 9000] + [1 << 16] * 30 + [(1 << 17) + 1, 1 << 17, 8192, 3] +
+            [40_001] * 9 + [1 << 14, 8193, 300_000],
+    "few": [8193, (1 << 19) + 77, 1 << 17, 100, (1 << 14) + 1, 0, 1 << 18],
+    "none": [1 << 17, 9000, 40_000, 100, (1 << 16) + 1, 0, 8193, 1 << 14],
+    "long": [1 << 18, (1 << 17) + 1],
+}
+
+
+@pytest.mark.parametrize("table", list(TABLES))
+@pytest.mark.parametrize("bound_log2", [20, 25])
+def test_each_segment_by_its_own_class(table, bound_log2):
+    B = _bind()
+    lens = TABLES[table]
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64) + 5
+    n = int(off[-1]) + 3
+    ot = torch.from_numpy(off).cuda()
+    arena = 1 << 22    # the table lies in a larger allocation
+    for i, type_ in enumerate(["int32", "uint32", "float32", "int64", "uint64", "float64"]):
+        asc = (i + bound_log2) % 2 == 0
+        w = W.splitmix64(9 + i, 0, n).view(np.int64)
+        k = w if i >= 3 else w.astype(np.int32)
+        t = torch.empty(arena, dtype=torch.int64 if i >= 3 else torch.int32, device="cuda")[:n]
+        t.copy_(torch.from_numpy(k.copy()))
+        B.bitonic_sort_segmented_keys(t, ot, asc, type_, 1 << bound_log2)
+        want = k.copy()
+        for a, b in zip(off[:-1], off[1:]):
+            want[a:b] = O.sort_keys64(k[a:b].view(type_), i, asc).view(np.int64) if i >= 3 else \
+                O.sort_keys(k[a:b].view(type_), i, asc).view(np.int32)
+        assert np.array_equal(t.cpu().numpy(), want), (type_, asc)
+
+
+@pytest.mark.parametrize("table", list(TABLES))
+@pytest.mark.parametrize("ordered", [True, False])
+def test_each_segment_by_its_own_class_pairs(table, ordered):
+    B = _bind()
+    lens = TABLES[table]
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    n = int(off[-1])
+    k = (W.uniform_i32(4, n) >> 20).astype(np.int32)      # many ties
+    v = np.arange(n, dtype=np.int32) if ordered else W.uniform_i32(5, n)
+    kt = torch.empty(1 << 22, dtype=torch.int32, device="cuda")[:n]
+    vt = torch.empty_like(kt)
+    kt.copy_(torch.from_numpy(k))
+    vt.copy_(torch.from_numpy(v))
+    B.bitonic_sort_segmented_pairs(kt, vt, torch.from_numpy(off).cuda(), True, "int32", 1 << 21)
+    for a, b in zip(off[:-1], off[1:]):
+        k[a:b], v[a:b] = O.sort_pairs(k[a:b], v[a:b], 0, True)
+    assert np.array_equal(kt.cpu().numpy(), k)
+    assert np.array_equal(vt.cpu().numpy(), v)
+
+
+def test_refused_table_touches_no_key():
+    """With validation on, a table with a segment above its bound leaves the
+    keys alone on this route too."""
+    B = _bind()
+    k = W.uniform_i32(6, 2_000_000)
+    t = torch.from_numpy(k.copy()).cuda()
+    off = torch.tensor([0, 300_000, 2_000_000], device="cuda")
+    B.bitonic_set_tuning_value("validate", 1)
+    try:
+        B.bitonic_validation_error()
+        B.bitonic_sort_segmented_keys(t, off, True, "int32", 1 << 20)
+        assert B.bitonic_validation_error() == 3
+        assert np.array_equal(t.cpu().numpy(), k)
+    finally:
+        B.bitonic_set_tuning_value("validate", 0)
