@@ -213,11 +213,11 @@ int64_t bitonic_segmented_default_bound(const void* keys, int key_bytes);
  * and the elements in all may be; if those of 2^13 + 1 to 2^17 elements are
  * few they go with them, otherwise the network sorts them as it does without
  * any longer one.  The workspace, as of a single array as long as all
- * segments together, is laid out for the smaller of nseg * max_seg_len and
- * the elements from `keys` to the end of their allocation, by the runtime's
- * records; where that is more than 2^28 elements, or cannot be had, the
- * network sorts all.  (bitonic_sort_segmented_noalloc_i32 and graphs always
- * run the network.)
+ * segments together, is laid out for nseg * max_seg_len elements (without a
+ * bound: those from `keys` to the end of their allocation), or for fewer
+ * where the caller gives their number (bitonic_sort_segmented_within); where
+ * that is more than 2^28 elements, or cannot be had, the network sorts all.
+ * (bitonic_sort_segmented_noalloc_i32 and graphs always run the network.)
  *
  * As bitonic_sort_segmented_i32, with a host-side bound: every segment holds
  * at most max_seg_len keys (0 = unknown: then the bound of
@@ -286,6 +286,18 @@ int bitonic_sort_segmented_keys(void* keys, const int64_t* offsets, int64_t nseg
 int bitonic_sort_segmented_pairs(void* keys, int32_t* values, const int64_t* offsets,
                                  int64_t nseg, int64_t max_seg_len, int key_type,
                                  int ascending, void* stream);
+
+/*
+ * The two calls above in one (values == NULL: keys of any type; else pairs
+ * with 4-byte keys), with a bound on the elements of all segments together:
+ * offsets[nseg] - offsets[0] <= total (0 = unknown).  It sizes the workspace
+ * of the digit sort, which nseg * max_seg_len may make several times larger
+ * than the segments, or too large to be taken.  A table that holds more than
+ * `total` is sorted all the same, its long segments slowly.
+ */
+int bitonic_sort_segmented_within(void* keys, int32_t* values, const int64_t* offsets,
+                                  int64_t nseg, int64_t max_seg_len, int64_t total, int key_type,
+                                  int ascending, void* stream);
 
 /*
  * Plans.  A plan fixes how the k(k+1)/2 steps of the network map onto

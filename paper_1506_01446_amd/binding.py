@@ -92,6 +92,9 @@ def load() -> ctypes.CDLL:
                                           ctypes.c_int, vp], ctypes.c_int),
         "bitonic_sort_segmented_keys": ([vp, vp, ctypes.c_int64, ctypes.c_int64, ctypes.c_int,
                                          ctypes.c_int, vp], ctypes.c_int),
+        "bitonic_sort_segmented_within": ([vp, vp, vp, ctypes.c_int64, ctypes.c_int64,
+                                           ctypes.c_int64, ctypes.c_int, ctypes.c_int, vp],
+                                          ctypes.c_int),
         "bitonic_plan_describe": ([ctypes.c_int64, ctypes.POINTER(bitonic_plan), vp, vp,
                                    ctypes.c_int64], ctypes.c_int64),
         "bitonic_sort_plan_launches_i32": ([vp, ctypes.c_int64, ctypes.c_int,
@@ -302,11 +305,15 @@ def bitonic_sort_segmented_pairs(keys, values, offsets, ascending: bool = True, 
     kp, vptr = _pair_ptrs(keys, values)
     op = _keys_ptr(offsets, "int64")
     nseg = max(offsets.numel() - 1, 0)
-    bound = _segment_bound(keys, max_seg_len)
-    _check("bitonic_sort_segmented_pairs",
-           load().bitonic_sort_segmented_pairs(kp, vptr, op, nseg, bound,
-                                               _key_type(keys, key_type), int(bool(ascending)),
-                                               _stream(stream)))
+    _segmented("bitonic_sort_segmented_pairs", kp, vptr, keys, op, nseg,
+               _segment_bound(keys, max_seg_len), _key_type(keys, key_type), ascending, stream)
+
+
+def _segmented(name, kp, vptr, keys, op, nseg, bound, key_type, ascending, stream) -> None:
+    """Segments lie inside `keys`: its length bounds their elements in all."""
+    _check(name, load().bitonic_sort_segmented_within(kp, vptr, op, nseg, bound, keys.numel(),
+                                                      key_type, int(bool(ascending)),
+                                                      _stream(stream)))
 
 
 def bitonic_sort_segmented_keys(keys, offsets, ascending: bool = True, key_type=None,
@@ -316,18 +323,11 @@ def bitonic_sort_segmented_keys(keys, offsets, ascending: bool = True, key_type=
     bound = _segment_bound(keys, max_seg_len)
     if keys.element_size() == 8:
         kp, kt = _any64_ptr(keys), _key_type64(keys, key_type)
-        op = _keys_ptr(offsets, "int64")
-        _check("bitonic_sort_segmented_keys",
-               load().bitonic_sort_segmented_keys(kp, op, max(offsets.numel() - 1, 0),
-                                                  bound, kt, int(bool(ascending)),
-                                                  _stream(stream)))
-        return
-    kp = _any32_ptr(keys)
+    else:
+        kp, kt = _any32_ptr(keys), _key_type(keys, key_type)
     op = _keys_ptr(offsets, "int64")
-    _check("bitonic_sort_segmented_keys",
-           load().bitonic_sort_segmented_keys(kp, op, max(offsets.numel() - 1, 0),
-                                              bound, _key_type(keys, key_type),
-                                              int(bool(ascending)), _stream(stream)))
+    _segmented("bitonic_sort_segmented_keys", kp, None, keys, op, max(offsets.numel() - 1, 0),
+               bound, kt, ascending, stream)
 
 
 def bitonic_sort_plan_i32(keys, ascending: bool = True, plan=None, stream=None) -> None:
@@ -355,10 +355,8 @@ def bitonic_sort_segmented_i32(keys, offsets, ascending: bool = True, stream=Non
     kp = _keys_ptr(keys)
     op = _keys_ptr(offsets, "int64")
     nseg = max(offsets.numel() - 1, 0)
-    _check("bitonic_sort_segmented_bounded_i32",
-           load().bitonic_sort_segmented_bounded_i32(kp, op, nseg,
-                                                     _segment_bound(keys, max_seg_len),
-                                                     int(bool(ascending)), _stream(stream)))
+    _segmented("bitonic_sort_segmented_bounded_i32", kp, None, keys, op, nseg,
+               _segment_bound(keys, max_seg_len), 0, ascending, stream)
 
 
 def bitonic_sort_segmented_noalloc_i32(keys, offsets, max_seg_len: int, ascending: bool = True,

@@ -526,7 +526,8 @@ static int seg_tile_log_of(const SegData& d) {
 static int64_t enqueue_segmented(const SegData& d, const int64_t* offsets, int64_t nseg,
                                  int64_t max_seg_len, void* scratch, int cus, hipStream_t st,
                                  bool count_only = false, Observer* obs = nullptr,
-                                 int unit = 4, const SegRadixSpace* digits = nullptr) {
+                                 int unit = 4, const SegRadixSpace* digits = nullptr,
+                                 int64_t elems = INT64_MAX / 4) {
   const int T = seg_tile_log_of(d);
   int64_t launches = 0;
   auto emit = [&](bitonic_launch_shape sh, auto&& launch) {
@@ -555,9 +556,14 @@ static int64_t enqueue_segmented(const SegData& d, const int64_t* offsets, int64
     M = kSegRadixMinClass - 1;
   }
   // two workgroups per CU of the 2^14-key tiles (67.6 KB of LDS each), four
-  // of the 2^13-element ones
-  const int grid = cus * (T == kSegTileLog32 ? 2 : 4);
-  const int pass_grid = cus * g_seg_pass_bpc.load();
+  // of the 2^13-element ones; no more than the units that `elems` elements can
+  // make (2^T-element tiles, 2^11-element passes of their padded lengths), as
+  // starting 4,096 workgroups that find nothing to do takes a microsecond
+  auto at_most = [](int g, int64_t units) { return units < g ? (int)units : g; };
+  const int64_t tiles = (elems >> T) + (elems >> kSegSmallMaxLog2) + 1;
+  const int grid = at_most(cus * (T == kSegTileLog32 ? 2 : 4), tiles);
+  const int phase_grid = at_most(T == kSegTileLog32 ? cus : 2 * cus, tiles);
+  const int pass_grid = at_most(cus * g_seg_pass_bpc.load(), (elems >> 10) + 1);
   emit({BITONIC_LAUNCH_TILE_SORT, 0, T, 0, unit, 64},
        [&] { launch_seg_tiles(false, d, offsets, sc, kSegSmallMaxLog2 + 1, grid, st); });
   const int fuse = g_seg_fuse.load();
@@ -568,7 +574,7 @@ static int64_t enqueue_segmented(const SegData& d, const int64_t* offsets, int64
       // one workgroup per CU for 4-byte keys (135 KiB of LDS), two for 8-byte
       // elements (68 KiB)
       emit({BITONIC_LAUNCH_TILE_MERGE, 0, p, 1, unit, 64},
-           [&] { launch_seg_phase(d, offsets, sc, T == kSegTileLog32 ? cus : 2 * cus, st); });
+           [&] { launch_seg_phase(d, offsets, sc, phase_grid, st); });
       continue;
     }
     const int nb = p - T;
@@ -1000,24 +1006,16 @@ static int64_t allocation_bound(const void* keys, int elem_bytes) {
   return elems < 1 ? 1 : (elems < cap ? elems : cap);
 }
 
-// A bound on the elements of all segments: they lie in the keys' allocation
-// and do not overlap, and none is longer than max_seg_len.
-static int64_t segmented_elems(const void* keys, int elem_bytes, int64_t nseg,
-                               int64_t max_seg_len) {
-  const int64_t in_allocation = allocation_bound(keys, elem_bytes);
-  const int64_t by_length = max_seg_len > INT64_MAX / nseg ? INT64_MAX : max_seg_len * nseg;
-  return in_allocation < by_length ? in_allocation : by_length;
-}
-
 // Segmented sort of keys of any key type (values == nullptr) or of (key,
 // value) pairs with 4-byte keys.
 static int sort_segmented(void* keys_v, int32_t* values, const int64_t* offsets, int64_t nseg,
-                          int64_t max_seg_len, int key_type, int ascending, void* stream) {
+                          int64_t max_seg_len, int64_t total, int key_type, int ascending,
+                          void* stream) {
   int32_t* keys = static_cast<int32_t*>(keys_v);
   if (key_type < BITONIC_KEY_I32 || key_type > BITONIC_KEY_F64) return BITONIC_EINVAL;
   const bool wide_keys = key_type >= BITONIC_KEY_I64;
   if (wide_keys && values != nullptr) return BITONIC_EINVAL;
-  if (nseg < 0 || max_seg_len < 0) return BITONIC_EINVAL;
+  if (nseg < 0 || max_seg_len < 0 || total < 0) return BITONIC_EINVAL;
   if (nseg >= (int64_t(1) << 31)) return BITONIC_EUNSUPPORTED;
   if (max_seg_len > (int64_t(1) << 31)) return BITONIC_EUNSUPPORTED;
   if (nseg == 0) return BITONIC_OK;
@@ -1030,7 +1028,9 @@ static int sort_segmented(void* keys_v, int32_t* values, const int64_t* offsets,
   int dev = 0;
   int rc = current_device(&dev);
   if (rc) return rc;
-  if (max_seg_len == 0) max_seg_len = allocation_bound(keys_v, wide_keys ? 8 : 4);
+  auto in_allocation = [&] { return allocation_bound(keys_v, wide_keys ? 8 : 4); };
+  const int64_t elems = seg_elems(nseg, max_seg_len, total, in_allocation);
+  if (max_seg_len == 0) max_seg_len = in_allocation();
   void* base = nullptr;
   rc = stream_scratch(dev, st, seg_scratch_bytes(nseg), &base);
   if (rc) return rc;
@@ -1050,21 +1050,20 @@ static int sort_segmented(void* keys_v, int32_t* values, const int64_t* offsets,
   void* ws = nullptr;
   size_t ws_bytes = 0;
   const int eb = d.keys64 || d.values ? 8 : 4;
-  const int64_t elems = segmented_elems(keys_v, wide_keys ? 8 : 4, nseg, max_seg_len);
   if (seg_digit_launches(max_seg_len, elems)) {
     ws_bytes = segradix_space(nullptr, elems, nseg, eb, nullptr);
     ws = g_workspaces.acquire(dev, st, ws_bytes, st != hipStreamPerThread);
     if (ws) segradix_space(static_cast<char*>(ws), elems, nseg, eb, &digits);
   }
   enqueue_segmented(d, offsets, nseg, max_seg_len, base, device_cus(dev), st, false, nullptr, 4,
-                    ws ? &digits : nullptr);
+                    ws ? &digits : nullptr, elems);
   if (ws) g_workspaces.release(dev, st, ws, ws_bytes);
   return finish_launches();
 }
 
 int bitonic_sort_segmented_keys(void* keys, const int64_t* offsets, int64_t nseg,
                                 int64_t max_seg_len, int key_type, int ascending, void* stream) {
-  return sort_segmented(keys, nullptr, offsets, nseg, max_seg_len, key_type, ascending, stream);
+  return sort_segmented(keys, nullptr, offsets, nseg, max_seg_len, 0, key_type, ascending, stream);
 }
 
 int bitonic_sort_segmented_pairs(void* keys, int32_t* values, const int64_t* offsets,
@@ -1072,7 +1071,14 @@ int bitonic_sort_segmented_pairs(void* keys, int32_t* values, const int64_t* off
                                  void* stream) {
   if (key_type < BITONIC_KEY_I32 || key_type > BITONIC_KEY_F32) return BITONIC_EINVAL;
   if (nseg > 0 && values == nullptr) return BITONIC_EINVAL;
-  return sort_segmented(keys, values, offsets, nseg, max_seg_len, key_type, ascending, stream);
+  return sort_segmented(keys, values, offsets, nseg, max_seg_len, 0, key_type, ascending, stream);
+}
+
+int bitonic_sort_segmented_within(void* keys, int32_t* values, const int64_t* offsets,
+                                  int64_t nseg, int64_t max_seg_len, int64_t total, int key_type,
+                                  int ascending, void* stream) {
+  return sort_segmented(keys, values, offsets, nseg, max_seg_len, total, key_type, ascending,
+                        stream);
 }
 
 int bitonic_validation_error(int32_t* code) {

@@ -19,11 +19,11 @@ constexpr int segradix_items() {
   return (1 << seg_tile_log<ST>()) / kRadixThreads;
 }
 
-// The workspace was laid out for a bound on the segments' elements that comes
-// from the runtime's record of the keys' allocation.  Should the table hold
-// more than that (a record of a part of the keys' memory), no kernel touches
-// the workspace's arrays past their ends: the segments are then sorted where
-// they are (segradix_in_place).
+// The workspace was laid out for a bound on the segments' elements (seg_elems):
+// the caller's word, or without a bound on their length the runtime's record of
+// the keys' allocation.  Should the table hold more than that, no kernel
+// touches the workspace's arrays past their ends: the segments are then sorted
+// where they are (segradix_in_place).
 __device__ __forceinline__ bool segradix_fits(const int64_t* offsets, const SegMeta* seg_meta,
                                               const uint64_t* big_tiles, const SegRadixSpace& s) {
   const uint32_t nbig = seg_meta->nradix;

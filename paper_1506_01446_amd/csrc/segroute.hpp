@@ -42,6 +42,19 @@ constexpr int64_t kSegRadixMaxElems = int64_t(1) << 28;
 // (4-byte keys; 8-byte elements 13 to 31), the digits 13 (31).
 constexpr uint64_t kSegRadixMaxMedium = uint64_t(1) << 21;
 
+// A bound on the elements of all segments, which the digit workspace is laid
+// out for.  total: the caller's, 0 if not given; in_allocation: the elements
+// to the end of the keys' allocation by the runtime's records, asked for only
+// where the bound on the length is taken from them too (max_seg_len == 0): a
+// record may cover a part of the keys' memory, and says nothing of a table in
+// a larger buffer.
+template <class F>
+constexpr int64_t seg_elems(int64_t nseg, int64_t max_seg_len, int64_t total, F in_allocation) {
+  if (max_seg_len == 0) return total ? total : (int64_t)in_allocation();
+  const int64_t by_length = max_seg_len > INT64_MAX / nseg ? INT64_MAX : max_seg_len * nseg;
+  return total && total < by_length ? total : by_length;
+}
+
 // Whether the digit launches are enqueued: by the caller's bound on the
 // segment length and a bound on the elements of all segments.
 constexpr bool seg_digit_launches(int64_t max_seg_len, int64_t elems) {

@@ -6,7 +6,7 @@ batches on the device.  Whenever a batch slot is free and the key arena (the
 HBM budget) has room, it packs pending requests, oldest first, into one
 batch: a contiguous arena region holding the requests' keys back to back,
 described by a CSR offset table, sorted with one segmented launch sequence
-(bitonic_sort_segmented_bounded_i32) on the slot's own stream.  Batches on
+(bitonic_sort_segmented_within) on the slot's own stream.  Batches on
 different streams overlap on the device; a request that arrives while others
 run is admitted as soon as a slot and memory free up (continuous batching,
 not a queue drained between batches).  A request larger than the whole
@@ -196,9 +196,10 @@ class GpuExecutor:
             rc = self.lib.bitonic_sort_i32(base, max_len, int(ascending), sp)
             name = "bitonic_sort_i32"
         else:
-            rc = self.lib.bitonic_sort_segmented_bounded_i32(base, od.data_ptr(), nseg,
-                                                             max(max_len, 1), int(ascending), sp)
-            name = "bitonic_sort_segmented_bounded_i32"
+            rc = self.lib.bitonic_sort_segmented_within(base, None, od.data_ptr(), nseg,
+                                                        max(max_len, 1), int(batch.offsets[-1]),
+                                                        0, int(ascending), sp)
+            name = "bitonic_sort_segmented_within"
             self.segmented_batches += 1
         if rc:
             raise B.BitonicError(name, rc)

@@ -56,6 +56,23 @@ int main() {
     cnt[18] = 1;
     CHECK(seg_digit_class(cnt) == kSegRadixMinClass);
   }
+  {  // elements: the runtime's records are asked for without a bound only
+    bool asked = false;
+    auto record = [&] {
+      asked = true;
+      return int64_t(5000);
+    };
+    CHECK(seg_elems(12, int64_t(1) << 22, 0, record) == int64_t(12) << 22 && !asked);
+    CHECK(seg_elems(100, int64_t(1) << 22, 11000000, record) == 11000000 && !asked);
+    CHECK(seg_elems(3, 100, 11000000, record) == 300 && !asked);
+    CHECK(seg_elems(int64_t(1) << 30, int64_t(1) << 31, 0, record) > kSegRadixMaxElems);
+    CHECK(seg_elems((int64_t(1) << 31) - 1, int64_t(1) << 31, 9, record) == 9 && !asked);
+    CHECK(seg_elems(7, 0, 123, record) == 123 && !asked);
+    CHECK(seg_elems(7, 0, 0, record) == 5000 && asked);
+    // a hundred requests with one of 2^22 keys, in a large arena
+    CHECK(!seg_digit_launches(1 << 22, seg_elems(100, 1 << 22, 0, record)));
+    CHECK(seg_digit_launches(1 << 22, seg_elems(100, 1 << 22, 30000000, record)));
+  }
   std::printf("ok\n");
   return 0;
 }

@@ -115,3 +115,28 @@ def test_refused_table_touches_no_key():
         assert np.array_equal(t.cpu().numpy(), k)
     finally:
         B.bitonic_set_tuning_value("validate", 0)
+
+
+@pytest.mark.parametrize("total", ["unknown", "exact", "too small"])
+@pytest.mark.parametrize("bounded", [True, False])
+def test_total_of_all_segments(total, bounded):
+    """The C entry with a bound on all segments' elements: it sizes the
+    workspace; one that the table exceeds costs time only."""
+    B = _bind()
+    lens = [700_001, 0, 9000, 64]
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64) + 11
+    n = int(off[-1])
+    k = W.uniform_i32(8, n)
+    t = torch.empty(1 << 22, dtype=torch.int32, device="cuda")
+    t[:n].copy_(torch.from_numpy(k))
+    ot = torch.from_numpy(off).cuda()
+    rc = B.load().bitonic_sort_segmented_within(
+        t.data_ptr(), None, ot.data_ptr(), len(lens), (1 << 20) if bounded else 0,
+        {"unknown": 0, "exact": n - 11, "too small": 600_000}[total], 0, 1,
+        torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    for a, b in zip(off[:-1], off[1:]):
+        k[a:b] = np.sort(k[a:b])
+    assert np.array_equal(t[:n].cpu().numpy(), k)
+    assert B.load().bitonic_sort_segmented_within(
+        t.data_ptr(), None, ot.data_ptr(), len(lens), 1 << 20, -1, 0, 1, None) == -1
