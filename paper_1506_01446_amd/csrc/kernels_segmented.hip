@@ -109,28 +109,13 @@ __global__ __launch_bounds__(1024) void seg_prep_kernel(const int64_t* __restric
   }
   if (tid < 32) cnt[tid] = 0;
   __syncthreads();
-  // The lengths of kBatch segments a thread at a time, their loads in flight
-  // together: the kernel is one workgroup and waits for nothing else.
-  constexpr int kBatch = 8;
-  auto each_segment = [&](auto&& f) {
-    for (int64_t s0 = tid; s0 < nseg; s0 += 1024 * kBatch) {
-      int64_t a[kBatch], b[kBatch];
-      static_for<0, kBatch>([&](auto k) {
-        const int64_t s = s0 + 1024 * k;
-        a[k] = s < nseg ? offsets[s] : 0;
-        b[k] = s < nseg ? offsets[s + 1] : 0;
-      });
-      static_for<0, kBatch>([&](auto k) {
-        const uint64_t len = (uint64_t)(b[k] - a[k]);
-        if (len > 1) f((uint32_t)(s0 + 1024 * k), len);
-      });
-    }
-  };
-  auto class_of = [](uint64_t len) {
-    const int c = ceil_log2_u64(len);
-    return c < 5 ? 5 : c;
-  };
-  each_segment([&](uint32_t, uint64_t len) { atomicAdd(&cnt[class_of(len)], 1u); });
+  for (int64_t s = tid; s < nseg; s += 1024) {
+    const uint64_t len = (uint64_t)(offsets[s + 1] - offsets[s]);
+    if (len <= 1) continue;
+    int c = ceil_log2_u64(len);
+    if (c < 5) c = 5;
+    atomicAdd(&cnt[c], 1u);
+  }
   __syncthreads();
   if (tid == 0) {
     // small buckets, class 13 first
@@ -167,14 +152,17 @@ __global__ __launch_bounds__(1024) void seg_prep_kernel(const int64_t* __restric
     nbig_s = bpos;
   }
   __syncthreads();
-  each_segment([&](uint32_t s, uint64_t len) {
-    const int c = class_of(len);
+  for (int64_t s = tid; s < nseg; s += 1024) {
+    const uint64_t len = (uint64_t)(offsets[s + 1] - offsets[s]);
+    if (len <= 1) continue;
+    int c = ceil_log2_u64(len);
+    if (c < 5) c = 5;
     const uint32_t slot = atomicAdd(&cur[c], 1u);
     if (c <= kSegSmallMaxLog2)
-      small_ids[slot] = s;
+      small_ids[slot] = (uint32_t)s;
     else
-      big_ids[slot] = s;
-  });
+      big_ids[slot] = (uint32_t)s;
+  }
   __syncthreads();
   // exclusive prefix sums over the big list (padded keys, real tiles)
   const uint32_t nbig = nbig_s;

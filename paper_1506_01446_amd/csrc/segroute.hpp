@@ -65,9 +65,9 @@ constexpr bool seg_digit_launches(int64_t max_seg_len, int64_t elems) {
 // The least class that goes by digits, given the number of segments of each
 // class; 32 if none does.
 constexpr int seg_digit_class(const uint32_t* segments_of) {
-  int top = 31;
-  while (top >= kSegRadixMinClass && segments_of[top] == 0) --top;
-  if (top < kSegRadixMinClass) return 32;
+  uint32_t longer = 0;
+  for (int c = kSegRadixMinClass; c < 32; ++c) longer |= segments_of[c];
+  if (longer == 0) return 32;
   uint64_t medium = 0;
   for (int c = kSegSmallMaxLog2 + 1; c < kSegRadixMinClass; ++c)
     medium += (uint64_t)segments_of[c] << c;
