@@ -94,20 +94,27 @@ struct SegData {
 };
 
 // Whether the small segments take the kernel for few of them (eight elements
-// per thread).  It is the faster one while the chip is not full of workgroups
-// of the other; 4-byte segments of up to 2^6 keys are a thread's or two's
-// registers there.  Measured on MI355X in us with the copy that restores the
-// input, kernel for many against few (and before it, 8-byte elements at 32
-// per thread):
-//   lengths to       2^5          2^8          2^11         2^13
-//   4-byte     64    16.7, 16.9   21.7, 18.0   28.1, 21.6   31.5, 27.4
-//             256    17.8, 18.4   24.1, 21.2   31.0, 24.6   34.9, 31.7
-//            8192    43.3, 43.3   46.1, 43.8   67.9, 84.3   298, 299
-//   8-byte     64    19.4, 18.0   27.4, 23.6   37.0, 33.0   47.2, 47.3 (86.4)
-//            2048    36.4, 34.5   49.4, 39.4   72.0, 68.6   125, 161  (204)
+// per thread).  Its workgroups are as large as the longest segment's (2^13
+// elements: 16 waves) and so fewer share a compute unit; it is the faster one
+// while the chip is not full of them.  4-byte segments of up to 2^6 keys are a
+// thread's or two's registers in the other, and a 2^13-key one is faster at 32
+// keys per thread.  Measured on MI355X in us with the copy that restores the
+// input, lengths between half of the longest and it (full: all the longest),
+// kernel for many against few:
+//   lengths to       2^7          2^9          2^11         2^12         2^13
+//   4-byte   1      17.4, 16.5   19.2, 15.4   18.5, 18.4   20.3, 20.0   22.3, 25.1
+//           64      19.3, 18.2   21.1, 17.3   21.8, 20.5   24.6, 23.2   26.2, 27.7
+//          256      21.4, 20.9   23.8, 20.3   25.0, 24.8   28.3, 28.3   33.9, 35.9
+//         1024      34.0, 32.6   39.5, 34.5   45.8, 48.8   57.8, 47.7   67.9, 115
+//   full  1024      33.2, 32.2   38.8, 34.7   46.6, 51.1   57.4, 48.1   67.9, 113
+//         4096      41.4, 41.5   51.9, 54.6   66.1, 98.3   155, 170
+//   8-byte  64      24.4, 21.5   28.5, 24.5   35.4, 33.5   40.5, 38.2   46.1, 48.2
+//          256      26.9, 24.7   31.7, 28.2   39.8, 38.1   46.2, 44.6   57.9, 59.3
+//         1024      43.1, 36.9   53.3, 45.1   72.6, 71.6   74.2, 73.0   152, 192
 constexpr bool seg_small_few(int64_t nseg, int max_log2, bool wide) {
   const int top = max_log2 < kSegSmallMaxLog2 ? max_log2 : kSegSmallMaxLog2;
-  return (wide || top > 6) && nseg < (int64_t(1) << (22 - top));
+  if (wide) return nseg < (int64_t(1) << (22 - top));
+  return top > 6 && top < kSegSmallMaxLog2 && nseg < (int64_t(1) << (20 - top));
 }
 
 // One launch of the sequence: the small-segment kernel, a big-segment tile

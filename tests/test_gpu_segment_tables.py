@@ -39,3 +39,17 @@ def test_table_sizes(nseg):
     lens[-1] = 9000
     _check(lens, "int32", 9000)
     _check(lens, "int64", 1 << 16)
+
+
+@pytest.mark.parametrize("type_", ["int32", "int64"])
+@pytest.mark.parametrize("top", [6, 7, 9, 11, 12, 13])
+def test_few_and_many_small_segments(type_, top):
+    """One segment below and at the number from which on a launch holds many,
+    full ones and lengths from one element on."""
+    edge = 1 << ((22 if type_ == "int64" else 20) - top)
+    for nseg in (edge - 1, edge, 3):
+        if nseg << top > 1 << 22:
+            continue
+        lens = 1 + (W.splitmix64(top, 0, nseg) % np.uint64(1 << top)).astype(np.int64)
+        lens[::3] = 1 << top
+        _check(lens, type_, 1 << top)
