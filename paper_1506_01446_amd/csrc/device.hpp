@@ -343,6 +343,14 @@ __device__ __forceinline__ void load_tile(int32_t (&x)[PR::R], const int32_t* __
     } else {
       static_for<0, PR::R>([&](auto J) { x[J] = cd.enc(tile[slot_index<PR, G, J>(base)]); });
     }
+  } else if constexpr (PR::VEC) {
+    // only the real keys are loaded: in the single arrays' programs, one
+    // partly filled tile a launch, that is faster than load_checked (MI355X,
+    // 2^14-key tiles: n = 20000 37.9 against 40.6 us, 400000 96.7 and 100.7)
+    static_for<0, PR::R>([&](auto J) {
+      const uint32_t i = slot_index<PR, G, J>(base);
+      x[J] = i < valid ? cd.enc(tile[i]) : kPad;
+    });
   } else {
     load_checked(x, valid, [&](auto J) { return slot_index<PR, G, J>(base); },
                  [&](uint32_t i) { return tile[i]; }, cd, kPad);
