@@ -480,7 +480,8 @@ static WorkspaceCache<PoolAlloc> g_workspaces;
 // and it can be had: middle sizes by rank (rank_pays), longer arrays by digits.
 // False (nothing enqueued) for sizes the network sorts faster, for n = 2^31, on
 // a stream that is being captured (the graph would share the stream's workspace
-// with later calls), and where the workspace cannot be allocated.
+// with later calls), and where the workspace cannot be allocated or allocating
+// it for one call costs more than it gives.
 static bool sort_through_workspace(const RadixData& d, int64_t n, hipStream_t st) {
   const int eb = d.keys64 || d.values ? 8 : 4;
   if (n <= 1 << 11 || n > kRadixMaxN) return false;
@@ -490,7 +491,8 @@ static bool sort_through_workspace(const RadixData& d, int64_t n, hipStream_t st
   if (stream_is_capturing(st) || current_device(&dev) != BITONIC_OK) return false;
   const size_t bytes =
       by_rank ? rank_workspace_bytes(n, eb) : radix_space(nullptr, (uint32_t)n, eb, nullptr);
-  void* const ws = g_workspaces.acquire(dev, st, bytes, st != hipStreamPerThread);
+  const bool only_kept = by_rank && !rank_pays_allocating(n, eb);
+  void* const ws = g_workspaces.acquire(dev, st, bytes, st != hipStreamPerThread, only_kept);
   if (!ws) return false;
   (void)hipGetLastError();
   if (by_rank)

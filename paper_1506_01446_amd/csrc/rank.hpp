@@ -41,6 +41,16 @@ constexpr int rank_tile_log2(int64_t n, int elem_bytes) {
 constexpr bool rank_pays(int64_t n, int elem_bytes, bool pairs) {
   return n > (elem_bytes == 4 ? 1 << 12 : 1 << 11) && n <= (pairs ? 1 << 16 : 1 << 17);
 }
+// Whether that is so even where the workspace has to be allocated and freed
+// for the call, which takes the host 17 us (on the per-thread stream, in a
+// second thread on one stream, on more streams than buffers are kept for).  A
+// whole call on MI355X in us, network against rank with that:
+//   4-byte keys  2^13  13.8, 24.8   2^14  19.2, 25.2   2^15  25.3, 26.3
+//                40000 44.3, 25.7   2^16  31.8, 24.7   2^17  39.2, 31.7
+//   8-byte keys  2^12  21.7, 24.2   6000  34.9, 24.7   2^14  50.2, 24.3
+constexpr bool rank_pays_allocating(int64_t n, int elem_bytes) {
+  return n > (elem_bytes == 4 ? 1 << 15 : 1 << 12);
+}
 constexpr uint32_t kRankMaxTiles = 32;
 static_assert(((1u << 17) - 1) >> rank_tile_log2(1 << 17, 8) < kRankMaxTiles &&
               ((1u << 17) - 1) >> rank_tile_log2(1 << 17, 4) < 16 &&

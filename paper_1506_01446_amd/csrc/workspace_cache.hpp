@@ -36,9 +36,10 @@ class WorkspaceCache {
 
   // A buffer of at least `bytes` for work on (dev, stream), nullptr if there
   // is none to be had.  keep == false: never a kept one (a stream handle that
-  // names another stream in every thread).  Every buffer is given back with
+  // names another stream in every thread).  only_kept: none that would be
+  // allocated and freed for this call.  Every buffer is given back with
   // release() once the call's work is enqueued.
-  void* acquire(int dev, void* stream, size_t bytes, bool keep = true) {
+  void* acquire(int dev, void* stream, size_t bytes, bool keep = true, bool only_kept = false) {
     std::lock_guard<std::mutex> lock(mu_);
     for (size_t i = 0; i < parked_.size(); ++i) {
       // a buffer whose free failed: its stream's work is still ordered
@@ -81,7 +82,7 @@ class WorkspaceCache {
         return p;
       }
     }
-    return alloc_.alloc(dev, stream, bytes);
+    return only_kept ? nullptr : alloc_.alloc(dev, stream, bytes);
   }
 
   // After the work that uses p is enqueued on (dev, stream).
