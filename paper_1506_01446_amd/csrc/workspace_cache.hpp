@@ -15,14 +15,16 @@
 #pragma once
 
 #include <stddef.h>
+#include <stdint.h>
 
 #include <mutex>
-#include <vector>
 
 namespace bitonic {
 
 // Alloc: `void* alloc(int dev, void* stream, size_t bytes)` (nullptr on
 // failure) and `bool free(int dev, void* stream, void* ptr)`, stream-ordered.
+// The cache itself allocates nothing and throws nothing (it runs under C
+// entries).
 template <class Alloc>
 class WorkspaceCache {
  public:
@@ -30,6 +32,7 @@ class WorkspaceCache {
   static constexpr size_t kKeepBytes = size_t(256) << 20;
   static constexpr size_t kKeepTotal = size_t(2) << 30;
   static constexpr size_t kKeepSlots = 32;
+  static constexpr size_t kParkSlots = 32;
   static constexpr int kShrinkCalls = 64;
 
   explicit WorkspaceCache(Alloc a = Alloc{}) : alloc_(a) {}
@@ -41,15 +44,14 @@ class WorkspaceCache {
   // release() once the call's work is enqueued.
   void* acquire(int dev, void* stream, size_t bytes, bool keep = true, bool only_kept = false) {
     std::lock_guard<std::mutex> lock(mu_);
-    for (size_t i = 0; i < parked_.size(); ++i) {
+    for (Slot& s : parked_) {
       // a buffer whose free failed: its stream's work is still ordered
-      Slot& s = parked_[i];
-      if (s.dev != dev || s.stream != stream || s.lent || !keep) continue;
+      if (!s.ptr || s.dev != dev || s.stream != stream || s.lent || !keep) continue;
       if (s.bytes >= bytes) {
         s.lent = true;
         return s.ptr;
       }
-      if (alloc_.free(dev, stream, s.ptr)) parked_.erase(parked_.begin() + (ptrdiff_t)i--);
+      if (alloc_.free(dev, stream, s.ptr)) s = Slot{};
     }
     if (keep && bytes <= kKeepBytes) {
       Slot* s = find(dev, stream);
@@ -73,13 +75,15 @@ class WorkspaceCache {
           }
           return nullptr;
         }
-      } else if (!s && slots_.size() < kKeepSlots && kept_ + rounded(bytes) <= kKeepTotal) {
-        const size_t want = rounded(bytes);
-        void* p = alloc_.alloc(dev, stream, want);
-        if (!p) return nullptr;
-        slots_.push_back(Slot{dev, stream, p, want, 0, true});
-        kept_ += want;
-        return p;
+      } else if (!s && kept_ + rounded(bytes) <= kKeepTotal) {
+        if (Slot* f = free_slot()) {
+          const size_t want = rounded(bytes);
+          void* p = alloc_.alloc(dev, stream, want);
+          if (!p) return nullptr;
+          *f = Slot{dev, stream, p, want, 0, true};
+          kept_ += want;
+          return p;
+        }
       }
     }
     return only_kept ? nullptr : alloc_.alloc(dev, stream, bytes);
@@ -88,48 +92,70 @@ class WorkspaceCache {
   // After the work that uses p is enqueued on (dev, stream).
   void release(int dev, void* stream, void* p, size_t bytes) {
     std::lock_guard<std::mutex> lock(mu_);
-    for (auto* list : {&slots_, &parked_})
-      for (Slot& s : *list)
-        if (s.ptr == p) {
-          s.lent = false;
-          return;
-        }
+    for (Slot& s : slots_)
+      if (s.ptr == p) {
+        s.lent = false;
+        return;
+      }
+    for (Slot& s : parked_)
+      if (s.ptr == p) {
+        s.lent = false;
+        return;
+      }
     give_back(Slot{dev, stream, p, bytes, 0, false});
   }
 
   size_t kept_bytes() const { return kept_; }
-  size_t kept_slots() const { return slots_.size(); }
-  size_t parked() const { return parked_.size(); }
+  size_t kept_slots() const { return used(slots_); }
+  size_t parked() const { return used(parked_); }
   Alloc& allocator() { return alloc_; }
 
  private:
   struct Slot {
-    int dev;
-    void* stream;
-    void* ptr;
-    size_t bytes;
-    int small;  // calls in a row that needed an eighth or less
-    bool lent;
+    int dev = 0;
+    void* stream = nullptr;
+    void* ptr = nullptr;  // nullptr: no buffer
+    size_t bytes = 0;
+    int small = 0;  // calls in a row that needed an eighth or less
+    bool lent = false;
   };
   static size_t rounded(size_t bytes) {
     size_t w = kMinBytes;
     while (w < bytes) w *= 2;
     return w;
   }
+  template <size_t N>
+  static size_t used(const Slot (&list)[N]) {
+    size_t n = 0;
+    for (const Slot& s : list) n += s.ptr != nullptr;
+    return n;
+  }
   Slot* find(int dev, const void* stream) {
     for (Slot& s : slots_)
-      if (s.dev == dev && s.stream == stream) return &s;
+      if (s.ptr && s.dev == dev && s.stream == stream) return &s;
+    return nullptr;
+  }
+  Slot* free_slot() {
+    for (Slot& s : slots_)
+      if (!s.ptr) return &s;
     return nullptr;
   }
   void give_back(Slot s) {
     s.lent = false;
-    if (!alloc_.free(s.dev, s.stream, s.ptr)) parked_.push_back(s);
+    if (alloc_.free(s.dev, s.stream, s.ptr)) return;
+    for (Slot& f : parked_)
+      if (!f.ptr) {
+        f = s;
+        return;
+      }
+    // more refused frees than can be kept account of: the buffer stays
+    // allocated
   }
 
   Alloc alloc_;
   std::mutex mu_;
-  std::vector<Slot> slots_;
-  std::vector<Slot> parked_;
+  Slot slots_[kKeepSlots];
+  Slot parked_[kParkSlots];
   size_t kept_ = 0;
 };
 
