@@ -54,9 +54,16 @@
  *    about 2 %, and 2 to 4 MiB) comes from a memory pool of the library.  A buffer of up to
  *    256 MiB is kept per (device, stream), at most 32 of them and 2 GiB in
  *    all, and given back for a smaller one when 64 calls in a row have needed
- *    an eighth of it or less; any other workspace is allocated for the call
- *    and freed in stream order behind it (the pool holds up to 4 GiB and
- *    returns what is above that at the next synchronisation).
+ *    an eighth of it or less.  When these are used up, a new stream's buffer
+ *    takes the place of that of the stream which has not sorted for longest,
+ *    if its sorts are done; to know that, calls enqueue a launch of one thread
+ *    more while over 16 buffers or 1 GiB are kept.  Any other workspace is
+ *    allocated for the call and freed in stream order behind it (the pool
+ *    holds up to 4 GiB and returns what is above that at the next
+ *    synchronisation).
+ *  - A stream may be destroyed once its sorts are done (hipStreamDestroy of the
+ *    present runtime waits for them): a later stream that gets the same handle
+ *    gets the same buffers.
  */
 #ifndef BITONIC_MI355X_H
 #define BITONIC_MI355X_H

@@ -431,6 +431,10 @@ static int stream_scratch(int dev, hipStream_t st, size_t bytes, void** out) {
 // may be capturing a graph, which these buffers are no part of.
 constexpr uint64_t kPoolKeep = uint64_t(4) << 30;
 
+__global__ void workspace_stamp_kernel(uint32_t* word, uint32_t value) {
+  __hip_atomic_store(word, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 struct PoolAlloc {
   struct Relaxed {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
@@ -473,8 +477,32 @@ struct PoolAlloc {
     (void)hipGetLastError();
     return false;
   }
+  // A word of host memory per kept buffer.
+  static constexpr size_t kWords = 32;
+  uint32_t* words = nullptr;
+  bool stamp(int, void* stream, int slot, uint32_t value) {
+    Relaxed relaxed;
+    if (!words) {
+      void* p = nullptr;
+      if (hipHostMalloc(&p, kWords * sizeof(uint32_t),
+                        hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+      }
+      words = static_cast<uint32_t*>(p);
+      for (size_t i = 0; i < kWords; ++i) words[i] = 0;
+    }
+    uint32_t* word = words + slot;
+    void* args[] = {&word, &value};
+    return hipLaunchKernel(reinterpret_cast<const void*>(&workspace_stamp_kernel), dim3(1),
+                           dim3(1), args, 0, (hipStream_t)stream) == hipSuccess;
+  }
+  uint32_t stamped(int slot) {
+    return words ? __atomic_load_n(words + slot, __ATOMIC_ACQUIRE) : 0;
+  }
 };
 static WorkspaceCache<PoolAlloc> g_workspaces;
+static_assert(WorkspaceCache<PoolAlloc>::kKeepSlots == PoolAlloc::kWords);
 
 // The sort of d's n elements through a workspace, where that is the faster way
 // and it can be had: middle sizes by rank (rank_pays), longer arrays by digits.

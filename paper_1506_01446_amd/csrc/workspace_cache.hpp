@@ -9,9 +9,10 @@
 // between this call's.
 //
 // What is kept is bounded: at most kKeepBytes a stream, kKeepTotal and
-// kKeepSlots in all.  Anything beyond is allocated for the one call and freed
-// in stream order behind it, and a stream whose calls have long needed an
-// eighth of its buffer or less gives it back for a smaller one.
+// kKeepSlots in all.  A new stream takes the place of the idle one that has
+// not sorted for longest.  Anything beyond is allocated for the one call and
+// freed in stream order behind it, and a stream whose calls have long needed
+// an eighth of its buffer or less gives it back for a smaller one.
 #pragma once
 
 #include <stddef.h>
@@ -22,9 +23,11 @@
 namespace bitonic {
 
 // Alloc: `void* alloc(int dev, void* stream, size_t bytes)` (nullptr on
-// failure) and `bool free(int dev, void* stream, void* ptr)`, stream-ordered.
-// The cache itself allocates nothing and throws nothing (it runs under C
-// entries).
+// failure) and `bool free(int dev, void* stream, void* ptr)`, stream-ordered;
+// for eviction, `bool stamp(int dev, void* stream, int slot, uint32_t value)`
+// (enqueues a write of value to the slot's word) and `uint32_t stamped(int
+// slot)` (the word as it is now).  The cache itself allocates nothing and
+// throws nothing (it runs under C entries).
 template <class Alloc>
 class WorkspaceCache {
  public:
@@ -34,6 +37,11 @@ class WorkspaceCache {
   static constexpr size_t kKeepSlots = 32;
   static constexpr size_t kParkSlots = 32;
   static constexpr int kShrinkCalls = 64;
+  // Above either, calls are stamped (crowded()).  A stamp is a launch of one
+  // thread, 2.5 us of the host's time, where allocating and freeing a workspace
+  // per call takes 17.
+  static constexpr size_t kQuietSlots = 16;
+  static constexpr size_t kQuietBytes = size_t(1) << 30;
 
   explicit WorkspaceCache(Alloc a = Alloc{}) : alloc_(a) {}
 
@@ -62,11 +70,14 @@ class WorkspaceCache {
           return s->ptr;
         }
         const size_t want = rounded(bytes);
-        if (kept_ - s->bytes + want <= kKeepTotal) {
+        s->lent = true;  // not to be evicted for itself
+        const bool room = make_room(dev, stream, kept_ - s->bytes, want);
+        s->lent = false;
+        if (room) {
           if (void* p = alloc_.alloc(dev, stream, want)) {
             give_back(*s);
             kept_ += want - s->bytes;
-            *s = Slot{dev, stream, p, want, 0, true};
+            *s = Slot{dev, stream, p, want, 0, true, 0, ++calls_};
             return p;
           }
           if (s->bytes >= bytes) {
@@ -75,12 +86,13 @@ class WorkspaceCache {
           }
           return nullptr;
         }
-      } else if (!s && kept_ + rounded(bytes) <= kKeepTotal) {
-        if (Slot* f = free_slot()) {
-          const size_t want = rounded(bytes);
+      } else if (!s) {
+        const size_t want = rounded(bytes);
+        if (make_room(dev, stream, kept_, want, true)) {
+          Slot* const f = free_slot();
           void* p = alloc_.alloc(dev, stream, want);
           if (!p) return nullptr;
-          *f = Slot{dev, stream, p, want, 0, true};
+          *f = Slot{dev, stream, p, want, 0, true, 0, ++calls_};
           kept_ += want;
           return p;
         }
@@ -95,6 +107,8 @@ class WorkspaceCache {
     for (Slot& s : slots_)
       if (s.ptr == p) {
         s.lent = false;
+        s.used = ++calls_;
+        s.stamp = crowded() ? stamp(s) : 0;
         return;
       }
     for (Slot& s : parked_)
@@ -102,7 +116,7 @@ class WorkspaceCache {
         s.lent = false;
         return;
       }
-    give_back(Slot{dev, stream, p, bytes, 0, false});
+    give_back(Slot{dev, stream, p, bytes});
   }
 
   size_t kept_bytes() const { return kept_; }
@@ -118,6 +132,10 @@ class WorkspaceCache {
     size_t bytes = 0;
     int small = 0;  // calls in a row that needed an eighth or less
     bool lent = false;
+    // what the slot's word becomes when its last call's work is done; 0: that
+    // call was not stamped
+    uint32_t stamp = 0;
+    uint64_t used = 0;  // order of the slots' last calls
   };
   static size_t rounded(size_t bytes) {
     size_t w = kMinBytes;
@@ -140,6 +158,44 @@ class WorkspaceCache {
       if (!s.ptr) return &s;
     return nullptr;
   }
+  // A stream may have been destroyed since its last sort, so nothing is asked
+  // of the streams of other slots: once many buffers are kept, a call on a kept
+  // one ends with a write to host memory, behind its work, and a slot whose
+  // write has arrived is idle.  Few streams, as most programs have, never pay
+  // for it; the slots they leave behind are at most kQuietSlots and kQuietBytes.
+  bool crowded() const { return used(slots_) > kQuietSlots || kept_ > kQuietBytes; }
+  uint32_t stamp(Slot& s) {
+    if constexpr (requires { alloc_.stamp(0, nullptr, 0, 0u); }) {
+      if (++last_stamp_ == 0) ++last_stamp_;
+      if (alloc_.stamp(s.dev, s.stream, (int)(&s - slots_), last_stamp_)) return last_stamp_;
+    }
+    return 0;
+  }
+  bool idle(const Slot& s) {
+    if constexpr (requires { alloc_.stamped(0); })
+      return s.stamp != 0 && alloc_.stamped((int)(&s - slots_)) == s.stamp;
+    return false;
+  }
+  // Whether `want` more bytes (and with `slot`, one more slot) fit beside
+  // `others` kept ones, after giving back, the longest unused first, as many
+  // idle buffers of the device as that takes.  They are freed on `stream`,
+  // where the caller is about to work.
+  bool make_room(int dev, void* stream, size_t others, size_t want, bool slot = false) {
+    while (others + want > kKeepTotal || (slot && !free_slot())) {
+      Slot* v = nullptr;
+      for (Slot& s : slots_)
+        if (s.ptr && s.dev == dev && !s.lent && idle(s) && (!v || s.used < v->used)) v = &s;
+      if (!v) return false;
+      const Slot gone = *v;
+      *v = Slot{};
+      kept_ -= gone.bytes;
+      others -= gone.bytes;
+      Slot freed = gone;
+      freed.stream = stream;
+      give_back(freed);
+    }
+    return true;
+  }
   void give_back(Slot s) {
     s.lent = false;
     if (alloc_.free(s.dev, s.stream, s.ptr)) return;
@@ -157,6 +213,8 @@ class WorkspaceCache {
   Slot slots_[kKeepSlots];
   Slot parked_[kParkSlots];
   size_t kept_ = 0;
+  uint64_t calls_ = 0;
+  uint32_t last_stamp_ = 0;
 };
 
 }  // namespace bitonic

@@ -51,3 +51,30 @@ def test_per_thread_stream(n):
         assert np.array_equal(w, want[::-1].astype(np.int64) * 3)
         assert np.array_equal(p, want)
         assert np.array_equal(v, np.argsort(keys[t], kind="stable").astype(np.int32))
+
+
+def test_streams_that_come_and_go():
+    """More streams than buffers are kept for, destroyed after use: sorts by
+    rank and by digits on each."""
+    import ctypes
+    B = _bind()
+    B.load()
+    rt = ctypes.CDLL("libamdhip64.so.7")   # the runtime the process has loaded
+    sizes = (6000, 140_001)
+    keys = {n: W.uniform_i32(n, n) for n in sizes}
+    want = {n: O.sort_i32(keys[n], True) for n in sizes}
+    for r in range(3):
+        streams = []
+        for _ in range(40):
+            h = ctypes.c_void_p()
+            assert rt.hipStreamCreateWithFlags(ctypes.byref(h), 1) == 0
+            streams.append(h)
+        work = [(n, torch.from_numpy(keys[n].copy()).cuda()) for n in sizes for _ in streams]
+        torch.cuda.synchronize()
+        for i, (n, t) in enumerate(work):
+            B.bitonic_sort_i32(t, True, stream=streams[i % 40].value)
+        torch.cuda.synchronize()
+        for n, t in work:
+            assert np.array_equal(t.cpu().numpy(), want[n]), (r, n)
+        for h in streams:
+            assert rt.hipStreamDestroy(h) == 0

@@ -20,3 +20,11 @@ def test_no_exception_without_host_memory(tmp_path):
                     "-o", exe, os.path.join(HERE, "workspace_noexcept_driver.cpp")], check=True)
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
+
+
+def test_idle_streams_make_room(tmp_path):
+    exe = str(tmp_path / "workspace_evict")
+    subprocess.run(["g++", "-std=c++20", "-O1", "-fsanitize=address,undefined",
+                    "-o", exe, os.path.join(HERE, "workspace_evict_driver.cpp")], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
