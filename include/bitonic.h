@@ -127,6 +127,15 @@ enum bitonic_key_type {
 int bitonic_sort_keys(void* keys, int64_t n, int key_type, int ascending, void* stream);
 
 /*
+ * Gives back the device memory that the library keeps as workspaces (see
+ * above) of all streams and devices, as far as no other thread is in a sort.
+ * Waits until the devices that hold any are idle; not to be called while a
+ * stream is being captured.  The next sorts allocate anew.
+ * Returns BITONIC_OK, or BITONIC_EDEVICE if some could not be given back.
+ */
+int bitonic_release_workspaces(void);
+
+/*
  * Sort n 8-byte keys in place: the network of sections 3.1-3.3 with the
  * tile sort and fused passes of sections 4.1-4.2 on 8-byte elements (longer
  * arrays by rank or digits, see above).

@@ -92,6 +92,7 @@ def load() -> ctypes.CDLL:
                                           ctypes.c_int, vp], ctypes.c_int),
         "bitonic_sort_segmented_keys": ([vp, vp, ctypes.c_int64, ctypes.c_int64, ctypes.c_int,
                                          ctypes.c_int, vp], ctypes.c_int),
+        "bitonic_release_workspaces": ([], ctypes.c_int),
         "bitonic_sort_segmented_within": ([vp, vp, vp, ctypes.c_int64, ctypes.c_int64,
                                            ctypes.c_int64, ctypes.c_int, ctypes.c_int, vp],
                                           ctypes.c_int),
@@ -285,6 +286,12 @@ def bitonic_sort_wide_plan(keys, values=None, ascending: bool = True, key_type=N
 def bitonic_wide_plan_passes(n: int, plan=None) -> int:
     p = _plan(plan)
     return int(load().bitonic_wide_plan_passes(int(n), _plan_ref(p)))
+
+
+def bitonic_release_workspaces() -> None:
+    """Gives back the device memory the library keeps as workspaces; waits
+    until the device is idle."""
+    _check("bitonic_release_workspaces", load().bitonic_release_workspaces())
 
 
 def _segment_bound(keys, max_seg_len) -> int:

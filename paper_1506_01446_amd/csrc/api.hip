@@ -477,6 +477,16 @@ struct PoolAlloc {
     (void)hipGetLastError();
     return false;
   }
+  // Back to the system, what the pools hold free.
+  bool trim() {
+    bool all = true;
+    for (hipMemPool_t p : pools)
+      if (p && hipMemPoolTrimTo(p, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        all = false;
+      }
+    return all;
+  }
   // A word of host memory per kept buffer.
   static constexpr size_t kWords = 32;
   uint32_t* words = nullptr;
@@ -1351,6 +1361,23 @@ int bitonic_load_tuning(const char* path) {
     if (r) rc = r;
   }
   return rc;
+}
+
+int bitonic_release_workspaces(void) {
+  int current = 0;
+  if (current_device(&current) != BITONIC_OK) return BITONIC_EDEVICE;
+  auto wait = [&](int dev) {
+    const bool ok = hipSetDevice(dev) == hipSuccess && hipDeviceSynchronize() == hipSuccess;
+    if (!ok) (void)hipGetLastError();
+    return ok;
+  };
+  // a second wait behind the frees: the pools give back what is free by then
+  const bool ok = g_workspaces.give_back_all(wait, [&](PoolAlloc& a) {
+    bool all = true;
+    for (int dev = 0; dev < kMaxDevices; ++dev) all = (!a.pools[dev] || wait(dev)) && all;
+    return all && a.trim();
+  });
+  return hipSetDevice(current) == hipSuccess && ok ? BITONIC_OK : BITONIC_EDEVICE;
 }
 
 int bitonic_graph_capture_sort_i32(bitonic_graph** out, int32_t* keys, int64_t n, int ascending,

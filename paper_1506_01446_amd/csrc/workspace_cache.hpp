@@ -119,6 +119,28 @@ class WorkspaceCache {
     give_back(Slot{dev, stream, p, bytes});
   }
 
+  // Gives back every buffer that is not lent.  wait(dev) waits until the
+  // device is idle; buffers of a device for which it fails stay.  Then
+  // after(allocator) runs, under the lock too.  False if anything stayed.
+  template <class Wait, class After>
+  bool give_back_all(Wait wait, After after) {
+    std::lock_guard<std::mutex> lock(mu_);
+    bool all = true;
+    auto sweep = [&](Slot& s, size_t counted) {
+      if (!s.ptr || s.lent) return;
+      // idle now, so it may be freed on the null stream: its own may be gone
+      if (wait(s.dev) && alloc_.free(s.dev, nullptr, s.ptr)) {
+        kept_ -= counted;
+        s = Slot{};
+      } else {
+        all = false;
+      }
+    };
+    for (Slot& s : slots_) sweep(s, s.bytes);
+    for (Slot& s : parked_) sweep(s, 0);
+    return after(alloc_) && all;
+  }
+
   size_t kept_bytes() const { return kept_; }
   size_t kept_slots() const { return used(slots_); }
   size_t parked() const { return used(parked_); }

@@ -78,3 +78,23 @@ def test_streams_that_come_and_go():
             assert np.array_equal(t.cpu().numpy(), want[n]), (r, n)
         for h in streams:
             assert rt.hipStreamDestroy(h) == 0
+
+
+def test_workspaces_are_given_back():
+    """The memory a large sort leaves with the library comes back."""
+    B = _bind()
+    n = 50_000_000
+    B.bitonic_release_workspaces()
+    t = torch.randint(-2**31, 2**31 - 1, (n,), dtype=torch.int32, device="cuda")
+    want = t.sort().values
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    B.bitonic_sort_i32(t, True)
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] <= before - 4 * n
+    B.bitonic_release_workspaces()
+    assert torch.cuda.mem_get_info()[0] >= before - (32 << 20)
+    assert torch.equal(t, want)
+    t = t.flip(0).contiguous()
+    B.bitonic_sort_i32(t, True)
+    assert torch.equal(t, want)

@@ -111,6 +111,21 @@ int main() {
     CHECK(use(c, 0, 41, MB) && use(c, 0, 41, Cache::kKeepBytes));
     CHECK(c.kept_bytes() <= Cache::kKeepTotal && c.allocator().bytes() == c.kept_bytes());
   }
+  {  // all given back but what is lent, or whose device cannot be waited for
+    Cache c;
+    for (size_t i = 1; i <= 5; ++i) CHECK(use(c, i == 3 ? 1 : 0, i, i * MB));
+    void* p = c.acquire(0, st(9), MB);
+    int waits = 0;
+    auto after = [&](Fake&) { return true; };
+    CHECK(!c.give_back_all([&](int dev) { return ++waits, dev == 0; }, after));
+    CHECK(waits == 5 && c.kept_slots() == 2 && c.kept_bytes() == 5 * MB);
+    CHECK(c.allocator().bytes() == c.kept_bytes() && c.allocator().freed_on == nullptr);
+    CHECK(c.give_back_all([&](int) { return true; }, after) && c.kept_slots() == 1);
+    c.release(0, st(9), p, MB);
+    CHECK(c.give_back_all([&](int) { return true; }, after));
+    CHECK(c.kept_bytes() == 0 && c.allocator().live.empty());
+    CHECK(use(c, 0, 9, MB) && c.kept_bytes() == MB);
+  }
   std::printf("ok\n");
   return 0;
 }
