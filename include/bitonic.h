@@ -499,7 +499,10 @@ int bitonic_sort_plan_launches_i32(int32_t* keys, int64_t n, int ascending,
                                    int64_t count, void* stream);
 
 /*
- * Tuning.  bitonic_set_tuning(tile_log2, fuse, merge_blocks_per_cu) changes
+ * Tuning, of the network: of all sorts that run it, by a plan, in a graph or
+ * for want of a workspace too, but not of those by rank or digits, so the plain
+ * sorts' times above 2^12 4-byte keys or 2^11 8-byte elements do not depend on
+ * it.  bitonic_set_tuning(tile_log2, fuse, merge_blocks_per_cu) changes
  * the library's default plan for BITONIC_PLAN_AUTO (values as in
  * bitonic_plan; 0 keeps the current value).  bitonic_set_tuning_value sets
  * one value by name: "tile_log2" (0 restores the choice by n), "fuse",
@@ -530,9 +533,9 @@ int bitonic_sort_plan_launches_i32(int32_t* keys, int64_t n, int ascending,
  * merges 2^t-key tiles -- one launch fewer than tiles of 2^t with the tile
  * phase, for a longer tile sort; for n a power of two on a 16-byte
  * boundary, with explicit optimized plans too),
- * "wide_tile_log2" (11..13) or
- * "wide_fuse" (1..8) (the 8-byte sorts' plan); bitonic_get_tuning_value
- * reads one.
+ * "wide_tile_log2" (11..13; until it is set, 13, but 11 from 2^12 to 2^16
+ * elements) or "wide_fuse" (1..8) (the 8-byte sorts' plan);
+ * bitonic_get_tuning_value reads one.
  * Size buckets: "tile_log2@k", "fuse@k", "merge_blocks_per_cu@k",
  * "lane_pass@k" and "sort_tile_log2@k" (k = ceil(log2 n), 0..31) set the
  * 4-byte sort's plan for that size only (0 removes the entry); a bucket's

@@ -287,7 +287,9 @@ def write_tuning(path: str, best: dict, command: str = "") -> None:
         for name in ("tile_log2", "fuse", "merge_blocks_per_cu", "lane_pass", "phase_blocks_per_cu",
                      "seg_blocks_per_cu",
                      "seg_pass_blocks_per_cu", "seg_fuse", "wide_tile_log2", "wide_fuse"):
-            if name in best:
+            # the 8-byte tile only where it is not the library's own choice,
+            # which is another one for short arrays
+            if name in best and (name, best[name]) != ("wide_tile_log2", 13):
                 f.write(f"{name} {best[name]}\n")
         for k, e in sorted(best.get("buckets", {}).items()):
             f.write(f"# n = 2^{k}: {e['ms']} ms tuned, {e['default_ms']} ms with the built-in plan\n")

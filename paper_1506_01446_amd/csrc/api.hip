@@ -42,7 +42,8 @@ namespace bitonic {
 static std::atomic<int> g_tile_log2{0};  // 0: by n (default_tile_log2)
 static std::atomic<int> g_fuse{10};
 static std::atomic<int> g_merge_bpc{2};  // 0: one tile per workgroup
-static std::atomic<int> g_wide_tile_log2{13};  // 8-byte sorts
+static std::atomic<int> g_wide_tile_log2{0};  // 8-byte sorts; 0: kWideTileDefault, or by n
+constexpr int kWideTileDefault = 13;
 static std::atomic<int> g_wide_fuse{8};
 static std::atomic<int> g_seg_bpc{4};    // small-segment workgroups per compute unit
 static std::atomic<int> g_seg_pass_bpc{8};  // big-segment pass workgroups per compute unit
@@ -747,11 +748,13 @@ static int resolve_wide(const bitonic_plan* plan, int64_t n, int* L, int* F) {
   load_env_tuning_once();
   *L = g_wide_tile_log2.load();
   *F = g_wide_fuse.load();
-  // Between one tile's size and 2^16 elements the smallest tiles: a larger one
-  // keeps fewer compute units busy for longer (int64 on MI355X, 2^13- against
-  // 2^11-element tiles: 2^13 34.7 and 25.9 us, 2^14 49.2 and 33.7, 2^16 74.0
-  // and 54.3).
-  if (n > int64_t(1) << kFewTilesMaxLog2 && n <= int64_t(1) << 16) *L = kWideTileMinLog2;
+  // Unless a tile is set, the smallest ones between one tile's size and 2^16
+  // elements: a larger one keeps fewer compute units busy for longer (int64 on
+  // MI355X, 2^13- against 2^11-element tiles: 2^13 34.7 and 25.9 us, 2^14 49.2
+  // and 33.7, 2^16 74.0 and 54.3).
+  if (*L == 0)
+    *L = n > int64_t(1) << kFewTilesMaxLog2 && n <= int64_t(1) << 16 ? kWideTileMinLog2
+                                                                      : kWideTileDefault;
   if (plan) {
     if (plan->kind != BITONIC_PLAN_AUTO && plan->kind != BITONIC_PLAN_OPTIMIZED)
       return BITONIC_EINVAL;
@@ -1312,7 +1315,8 @@ int bitonic_get_tuning_value(const char* key, int* value) {
   else if (!std::strcmp(key, "phase_merge")) *value = g_phase_merge.load();
   else if (!std::strcmp(key, "phase_blocks_per_cu")) *value = g_phase_bpc.load();
   else if (!std::strcmp(key, "validate")) *value = validate_enabled() ? 1 : 0;
-  else if (!std::strcmp(key, "wide_tile_log2")) *value = g_wide_tile_log2.load();
+  else if (!std::strcmp(key, "wide_tile_log2"))
+    *value = g_wide_tile_log2.load() ? g_wide_tile_log2.load() : kWideTileDefault;
   else if (!std::strcmp(key, "wide_fuse")) *value = g_wide_fuse.load();
   else return BITONIC_EINVAL;
   return BITONIC_OK;
