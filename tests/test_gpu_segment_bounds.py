@@ -140,3 +140,50 @@ def test_total_of_all_segments(total, bounded):
     assert np.array_equal(t[:n].cpu().numpy(), k)
     assert B.load().bitonic_sort_segmented_within(
         t.data_ptr(), None, ot.data_ptr(), len(lens), 1 << 20, -1, 0, 1, None) == -1
+
+
+# Around the tiles (2^14 4-byte, 2^13 8-byte elements), a group of 16 and a
+# supergroup of 256 of them.
+TILES = {
+    "classes": [(1 << 17) + 1, 0, 8193, 5, 8192, 1 << 14, (1 << 14) + 1, 70_001],
+    "tiles": [1 << 18, 1, (1 << 18) + 1, 3 * 8192, 300, 0, 150_000],
+    "supergroup": [(1 << 21) + 8193, 20_000, 1 << 17],
+}
+
+
+@pytest.mark.parametrize("lens", list(TILES.values()), ids=list(TILES))
+def test_segments_by_digits(lens):
+    """With room for more elements than there are, tables of fewer than 2^19
+    elements go by digits too."""
+    B = _bind()
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64) + 3
+    n = int(off[-1]) + 5
+    ot = torch.from_numpy(off).cuda()
+    st = torch.cuda.current_stream().cuda_stream
+    for i, type_ in enumerate(["int32", "uint32", "float32", "int64", "uint64", "float64"]):
+        for kind in ("uniform", "few"):
+            asc = (i % 2 == 0) == (kind == "few")
+            w = W.splitmix64(70 + i, 0, n).view(np.int64)
+            if kind == "few":
+                w = w & np.int64(0x0000FF000000FF00)
+            k = w.copy() if i >= 3 else w.astype(np.int32)
+            t = torch.from_numpy(k.copy()).cuda()
+            assert B.load().bitonic_sort_segmented_within(
+                t.data_ptr(), None, ot.data_ptr(), len(lens), 1 << 22, 1 << 22, i, int(asc),
+                st) == 0
+            for a, b in zip(off[:-1], off[1:]):
+                k[a:b] = O.sort_keys64(k[a:b].view(type_), i, asc).view(np.int64) if i >= 3 else \
+                    O.sort_keys(k[a:b].view(type_), i, asc).view(np.int32)
+            assert np.array_equal(t.cpu().numpy(), k), (type_, kind, asc)
+    k = (W.uniform_i32(31, n) >> 22).astype(np.int32)
+    v = W.uniform_i32(77, n)
+    for s, (a, b) in enumerate(zip(off[:-1], off[1:])):
+        if s % 2 == 0:    # in order in every other segment
+            v[a:b] = np.arange(b - a, dtype=np.int32)
+    kt, vt = torch.from_numpy(k.copy()).cuda(), torch.from_numpy(v.copy()).cuda()
+    assert B.load().bitonic_sort_segmented_within(
+        kt.data_ptr(), vt.data_ptr(), ot.data_ptr(), len(lens), 1 << 22, 1 << 22, 0, 0, st) == 0
+    for a, b in zip(off[:-1], off[1:]):
+        k[a:b], v[a:b] = O.sort_pairs(k[a:b], v[a:b], 0, False)
+    assert np.array_equal(kt.cpu().numpy(), k)
+    assert np.array_equal(vt.cpu().numpy(), v)
