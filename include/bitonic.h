@@ -224,11 +224,11 @@ int bitonic_validation_error(int32_t* code);
 int64_t bitonic_segmented_default_bound(const void* keys, int key_bytes);
 
 /*
- * Segments of more than 2^17 elements go by their digits, as long single
- * arrays do, when the bound (or what stands for it, see below) is above 2^19
- * and the elements in all may be; if those of 2^13 + 1 to 2^17 elements are
- * few they go with them, otherwise the network sorts them as it does without
- * any longer one.  The workspace, as of a single array as long as all
+ * Segments of more than 2^16 4-byte keys or 2^17 8-byte elements go by their
+ * digits, as long single arrays do, when the bound (or what stands for it, see
+ * below) is above 2^18 (2^19) and the elements in all may be; if the shorter
+ * ones above 2^13 are few they go with them, otherwise the network sorts them
+ * as it does without any longer one.  The workspace, as of a single array as long as all
  * segments together, is laid out for nseg * max_seg_len elements (without a
  * bound: those from `keys` to the end of their allocation), or for fewer
  * where the caller gives their number (bitonic_sort_segmented_within); where
@@ -244,7 +244,7 @@ int64_t bitonic_segmented_default_bound(const void* keys, int key_bytes);
  * plus, per phase p = 14 .. ceil(log2 bound), its fused long-stride passes
  * (at most "seg_fuse" steps each, default 5) and one tile merge; with the
  * digit sort its launches (one per digit and two) take the place of the
- * phases above 17.  Launches that find no segment of theirs take 2 to 2.5
+ * phases above 16 (17).  Launches that find no segment of theirs take 2 to 2.5
  * microseconds each.  Like
  * bitonic_sort_segmented_i32 it refuses a capturing stream.
  */

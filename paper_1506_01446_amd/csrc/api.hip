@@ -594,7 +594,7 @@ static int64_t enqueue_segmented(const SegData& d, const int64_t* offsets, int64
   if (M <= kSegSmallMaxLog2) return launches;
   if (digits) {
     launch_segradix(d, offsets, sc, *digits, cus, st);
-    M = kSegRadixMinClass - 1;
+    M = seg_radix_min_class(T == kSegTileLog64) - 1;
   }
   // two workgroups per CU of the 2^14-key tiles (67.6 KB of LDS each), four
   // of the 2^13-element ones; no more than the units that `elems` elements can
@@ -1093,7 +1093,7 @@ static int sort_segmented(void* keys_v, int32_t* values, const int64_t* offsets,
   void* ws = nullptr;
   size_t ws_bytes = 0;
   const int eb = d.keys64 || d.values ? 8 : 4;
-  if (seg_digit_launches(max_seg_len, elems)) {
+  if (seg_digit_launches(max_seg_len, elems, eb == 8)) {
     ws_bytes = segradix_space(nullptr, elems, nseg, eb, nullptr);
     ws = g_workspaces.acquire(dev, st, ws_bytes, st != hipStreamPerThread);
     if (ws) segradix_space(static_cast<char*>(ws), elems, nseg, eb, &digits);

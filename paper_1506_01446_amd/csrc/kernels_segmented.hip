@@ -134,7 +134,7 @@ __global__ __launch_bounds__(1024) void seg_prep_kernel(const int64_t* __restric
     meta->small_items = items;
     meta->small_counter = 0;
     // big buckets, largest class first
-    const int digit_cls = any_unordered ? seg_digit_class(cnt) : 32;
+    const int digit_cls = any_unordered ? seg_digit_class(cnt, tile_log == kSegTileLog64) : 32;
     uint32_t bpos = 0, nradix = 0;
     int maxc = 0;
     for (int c = 31; c > kSegSmallMaxLog2; --c) {

@@ -44,7 +44,7 @@ def test_small_arrays_with_loose_bounds(type_, lens, bound_log2):
     assert np.array_equal(t.cpu().numpy(), want)
 
 
-# Segments for the network (classes 14 to 17), for the digits (18 and above)
+# Segments for the network (up to class 16, of 8-byte elements 17), for the digits (above)
 # and for neither (2^13 and below), with the long ones first, last and
 # between; "many" has enough of the middle classes for the network to keep
 # them beside the digits' launches, "few" has not, "none" has no long one.
