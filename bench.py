@@ -515,8 +515,8 @@ def batched_vs_looped(torch, B, W):
             "eager_bounded_ms": round(eager_bounded_ms, 3),
             "eager_unbounded_ms": round(eager_unbounded_ms, 3),
             "unbounded_bound": buf.untyped_storage().nbytes() // 4 - buf.storage_offset(),
-            # the network's up to 2^17-key segments and the digit sort's count, scan and passes
-            "unbounded_launches": len(B.bitonic_plan_shapes(1 << 17, "seg_keys32")) + 6,
+            # the network's up to 2^16-key segments and the digit sort's count, scan and passes
+            "unbounded_launches": len(B.bitonic_plan_shapes(1 << 16, "seg_keys32")) + 6,
             "bounded_launches": len(B.bitonic_plan_shapes(mx, "seg_keys32")),
             "looped_eager_ms": round(looped_ms, 3),
             "looped_graph_ms": None if graph_ms is None else round(graph_ms, 3),

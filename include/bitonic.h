@@ -23,8 +23,9 @@
  *    place among all of them), and the longest by their digits, least
  *    significant first.  The result is the same (it is unique).  They run the
  *    network at every size where the workspace cannot be allocated, on a
- *    stream that is being captured into a graph, and for n = 2^31.  The calls
- *    that take a plan always run the network.
+ *    stream that is being captured into a graph, and for n = 2^31; and up to
+ *    2^15 4-byte keys or 2^12 8-byte elements where none is kept for the stream
+ *    (see below).  The calls that take a plan always run the network.
  *  - `stream` is a hipStream_t (NULL = the legacy default stream).  Calls are
  *    asynchronous: they enqueue kernels on `stream` and return; the keys are
  *    sorted once the stream reaches that point.  The host never blocks.
@@ -218,8 +219,8 @@ int bitonic_validation_error(int32_t* code);
  * 2^31 (2^31 where the allocation is unknown).  Host-side; nothing is
  * enqueued.  -1 for a NULL pointer or another key size.  The merge phases
  * enqueued are those up to ceil(log2 bound) (bitonic_plan_shapes with a
- * segmented layout and n = bound lists the launches), or up to 2^17 where
- * longer segments go by digits.
+ * segmented layout and n = bound lists the launches), or up to 16 (8-byte
+ * elements 17) where longer segments go by digits.
  */
 int64_t bitonic_segmented_default_bound(const void* keys, int key_bytes);
 

@@ -298,7 +298,8 @@ def _segment_bound(keys, max_seg_len) -> int:
     """The caller's bound on the segment length, or else the elements from
     the tensor's first to the end of its storage: segments lie inside it, and
     an allocator's blocks, whose size the library would take, are larger (by
-    2 to 20 MiB: up to ten merge phases that find no segment)."""
+    2 to 20 MiB: up to ten merge phases that find no segment).  The library
+    takes either for a bound, not for a length."""
     if max_seg_len or not keys.numel():
         return int(max_seg_len or 0)
     size = keys.element_size()

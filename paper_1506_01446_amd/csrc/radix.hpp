@@ -1,8 +1,11 @@
 // Sort of a long single array by its digits (internal interface): least
 // significant digit first, eight bits a pass, out of place between the array
 // and a workspace of its size (radix_kernels.hpp).  The plain sorts take it
-// where it is faster than the network (api.hip, radix_min_log2); explicit
-// plans always run the network.
+// above the sizes that go by rank (rank_pays); explicit plans always run the
+// network.  The method is published: radix sorts whose passes chain their
+// prefix sums through device memory (Merrill and Garland 2016, "Single-pass
+// Parallel Prefix Scan with Decoupled Look-back"; Adinets and Merrill 2022,
+// "Onesweep"), with equal digits of a wave found by ballots.
 #pragma once
 
 #include <hip/hip_runtime.h>

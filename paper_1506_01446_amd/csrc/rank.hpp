@@ -33,11 +33,15 @@ constexpr int rank_tile_log2(int64_t n, int elem_bytes) {
 
 // Whether n elements are sorted this way: more than one launch of the network
 // sorts (4-byte keys 2^12, 8-byte elements 2^11), and fewer than the digit
-// sort is faster for.  Measured in us, rank against digits:
-//   4-byte keys  70000  22.5, 37.0    100000  28.2, 37.2    2^17  32.1, 37.7
-//   8-byte keys  70000  35.6, 61.5    100000  42.2, 63.2    2^17  48.0, 64.3
-//   pairs        2^16   28.0, 43.3 (values in order), 62.7
-//                2^17   57.5, 45.5 and 66.6
+// sort is faster for.  Measured in us between two events (6 us of them the
+// events'), network, rank and digits:
+//   4-byte keys  4097   17.6, 14.6, 37.3   2^16    34.6, 23.5, 43.9
+//                70000  56.4, 29.5, 43.7   2^17    45.1, 38.4, 44.6
+//   8-byte keys  2049   22.6, 17.8, 56.7   2^16    58.6, 33.4, 70.8
+//                70000  93.1, 42.4, 72.2   2^17    93.5, 51.5, 76.3
+//   pairs        2049   23.0, 18.1, 62.3   2^16    57.8, 35.5, 74.3
+//   (digits of pairs with values in order 52.7 and 59.3)
+// At 2^17 pairs 32 tiles' searches took 57.5 against 45.5 and 66.6 by digits.
 constexpr bool rank_pays(int64_t n, int elem_bytes, bool pairs) {
   return n > (elem_bytes == 4 ? 1 << 12 : 1 << 11) && n <= (pairs ? 1 << 16 : 1 << 17);
 }
